@@ -151,14 +151,16 @@ enum {
                                 /* multi-kernel path, parallel over layers, is  */
                                 /* faster                                       */
 #define MD_FLAG_NO_ROW_GROUPS 0x20 /* keep every fused unit on all L Hkv rows. */
-                                /* By default, on plain pages with one query   */
-                                /* per observation, a step whose units would   */
-                                /* fill less than half of the fused kernel's   */
-                                /* grid splits each unit's rows into up to 16  */
-                                /* groups of at least 8 rows, one workgroup    */
-                                /* each, whose partial masses (over disjoint   */
-                                /* rows of Sec. III-C's mean) are added in a   */
-                                /* fixed order; results agree to rounding      */
+                                /* By default a step whose units would fill     */
+                                /* less than half of the fused kernel's grid    */
+                                /* splits each unit's rows into up to 16        */
+                                /* groups of at least 8 rows, one workgroup     */
+                                /* each, whose partial masses (over disjoint    */
+                                /* rows of Sec. III-C's mean) are added in a    */
+                                /* fixed order; so do the units of a step's     */
+                                /* last pass (at least 4 rows) when it would    */
+                                /* leave most of the grid idle.  Results agree  */
+                                /* to rounding                                  */
 
 typedef struct md_config {
     int32_t n_layers;           /* L                                              */

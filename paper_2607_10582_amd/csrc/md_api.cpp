@@ -309,28 +309,19 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     const int n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     int occ = 0;
     dm.T = md::attend_unit_tokens(dm.G);
-    // Row groups (plain pages, one query per observation): their own
-    // instantiation, used only if it is as resident as the plain one.
-    bool rows_ok = dm.fused && !dm.aligned && !dm.quant && dm.W == 1 && !(cfg->flags & MD_FLAG_NO_ROW_GROUPS) &&
-                   dm.LHkv >= 2 * md::kMinGroupRows;
+    // Row groups, of every unit of a step (a step that would fill less than
+    // half of the grid) or of its last pass.
+    const bool rows_ok = !(cfg->flags & MD_FLAG_NO_ROW_GROUPS);
     if (dm.fused) {
         const size_t lds = md::attend_lds_bytes(dm.G * dm.W);
-        auto occupancy = [&](int rg, int* o) {
-            const void* fn = md::attend_kernel(dm.G * dm.W, dm.aligned, dm.quant, dm.W, rg);
-            *o = 0;
-            if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-                (void)hipGetLastError();
-                return hipSuccess;
-            }
-            return hipOccupancyMaxActiveBlocksPerMultiprocessor(o, fn, md::attend_threads(dm.G * dm.W), lds);
-        };
-        if (occupancy(1, &occ) != hipSuccess) return MD_E_HIP;
-        if (occ > md::kAttendPerCu) occ = md::kAttendPerCu;
-        if (rows_ok) {
-            int occ_rg = 0;
-            if (occupancy(2, &occ_rg) != hipSuccess) return MD_E_HIP;
-            rows_ok = occ_rg >= occ;
+        const void* fn = md::attend_kernel(dm.G * dm.W, dm.aligned, dm.quant, dm.W);
+        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+            (void)hipGetLastError();
+        } else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, md::attend_threads(dm.G * dm.W), lds) !=
+                   hipSuccess) {
+            return MD_E_HIP;
         }
+        if (occ > md::kAttendPerCu) occ = md::kAttendPerCu;
         dm.n_wg = occ * n_cu;
         dm.fused = occ >= 1;
     }
@@ -343,18 +334,13 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     // be resident together: check it on the device, with the launch kind the
     // step uses, and step the grid down one workgroup per CU at a time until
     // every workgroup arrives.
-    int32_t* probe = nullptr;   // kept for the row-group instantiation's check below
-    auto free_probe = [&] {
-        if (!use_static && probe != nullptr) (void)hipFree(probe);
-        probe = nullptr;
-    };
     if (dm.fused) {
-        probe = static_cast<int32_t*>(static_base);   // the static scratch is free until carved
+        int32_t* probe = static_cast<int32_t*>(static_base);   // the static scratch is free until carved
         if (!use_static && hipMalloc(&probe, 2 * sizeof(int32_t)) != hipSuccess) return MD_E_NOMEM;
         int verified = 0;
         for (int o = occ; o >= 1 && verified == 0; --o) {
             int32_t seen[2] = {0, 0};
-            if (md::launch_attend_check(dm, probe, o * n_cu, 1, hs) != hipSuccess ||
+            if (md::launch_attend_check(dm, probe, o * n_cu, hs) != hipSuccess ||
                 hipMemcpyAsync(seen, probe, sizeof(seen), hipMemcpyDeviceToHost, hs) != hipSuccess ||
                 hipStreamSynchronize(hs) != hipSuccess) {
                 (void)hipGetLastError();
@@ -362,6 +348,7 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
             }
             if (seen[1] >= o * n_cu) verified = o * n_cu;
         }
+        if (!use_static) (void)hipFree(probe);
         dm.n_wg = verified;
         dm.wg_per_cu = verified / n_cu;
         dm.lane_cap = n_cu;
@@ -389,10 +376,8 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         if (hipMemcpyAsync(hn, cv->n_tokens, dm.S * sizeof(int32_t), hipMemcpyDeviceToHost, hs) != hipSuccess ||
             hipMemcpyAsync(hbud, cv->budget, dm.S * sizeof(int32_t), hipMemcpyDeviceToHost, hs) !=
                 hipSuccess ||
-            hipStreamSynchronize(hs) != hipSuccess) {
-            free_probe();
+            hipStreamSynchronize(hs) != hipSuccess)
             return MD_E_HIP;
-        }
         int64_t first = 0, steady = 0;
         for (int s = 0; s < dm.S; ++s) {
             const int64_t n = hn[s] > 0 ? hn[s] : 0;
@@ -401,7 +386,8 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
             steady += (std::min(n, b) + dm.T - 1) / dm.T;
         }
         const int64_t cap_units = ((int64_t)dm.MP * dm.P + dm.T - 1) / dm.T;
-        const int64_t rg_allow = rows_ok ? std::min<int64_t>({md::kMaxRowGroups, dm.LHkv / md::kMinGroupRows,
+        const int64_t rg_allow = rows_ok && dm.LHkv >= 2 * md::kMinGroupRows
+                                     ? std::min<int64_t>({md::kMaxRowGroups, dm.LHkv / md::kMinGroupRows,
                                                               dm.n_wg / std::max<int64_t>(cap_units, 1)})
                                          : 1;
         auto pick = [&](int64_t u) -> int {
@@ -410,20 +396,6 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         };
         rg_first = pick(first);
         rg_steady = pick(steady);
-        // the row-group instantiation, when a step will use it, must hold
-        // the same grid as the plain one
-        if (std::max(rg_first, rg_steady) > 1) {
-            int32_t seen[2] = {0, 0};
-            bool held = false;
-            if (md::launch_attend_check(dm, probe, dm.n_wg, 2, hs) != hipSuccess ||
-                hipMemcpyAsync(seen, probe, sizeof(seen), hipMemcpyDeviceToHost, hs) != hipSuccess ||
-                hipStreamSynchronize(hs) != hipSuccess) {
-                (void)hipGetLastError();
-            } else {
-                held = seen[1] >= dm.n_wg;
-            }
-            if (!held) rg_first = rg_steady = 1;
-        }
         // Units on every row pay off from half the grid on; row groups, whose
         // units walk few rows, from a quarter (measured on batches of
         // 1,700-token sessions: 8 sessions, 144 units of nine groups, 49.5
@@ -437,12 +409,22 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         if (!fused_first) rg_first = 1;
         if (!fused_steady) rg_steady = 1;
     }
-    free_probe();
     dm.rg_max = std::max(rg_first, rg_steady);
     if (dm.fused) dm.U_cap *= dm.rg_max;
     dm.multi = dm.spill || !fused_first || !fused_steady;
 
-    const size_t bytes = md::scratch_bytes(dm);
+    // Units of a last pass that fills little of the grid split too (at most
+    // the grid's worth more of them), unless the static scratch, large enough
+    // for the plain plan, cannot hold their statistics and partial masses.
+    const int plain_units = dm.U_cap;
+    dm.tail = rows_ok && dm.fused ? std::min(md::kMaxRowGroups, dm.LHkv / md::kMinTailRows) : 1;
+    if (dm.tail > 1) dm.U_cap += dm.n_wg; else dm.tail = 1;
+    size_t bytes = md::scratch_bytes(dm);
+    if (use_static && dm.tail > 1 && bytes > md::kStaticScratchBytes) {
+        dm.tail = 1;
+        dm.U_cap = plain_units;
+        bytes = md::scratch_bytes(dm);
+    }
     if (use_static && bytes > md::kStaticScratchBytes) return MD_E_TOO_LARGE;
     md_handle_s* h = use_static ? take_static_handle() : new (std::nothrow) md_handle_s();
     if (h == nullptr) return use_static ? MD_E_TOO_LARGE : MD_E_NOMEM;
@@ -566,7 +548,7 @@ md_status md_observe_step(md_handle h, int32_t step, const float* q, const uint1
     const bool multi = !fused || h->dm.spill;
     if (e == hipSuccess && fused)
         e = timed_launch_ev(h, MD_K_ATTEND, !h->dm.coop, [&](hipEvent_t t0, hipEvent_t t1) {
-            return md::launch_attend(h->dm, h->v, h->sc, q, abar_out, rg, h->stream, t0, t1); });
+            return md::launch_attend(h->dm, h->v, h->sc, q, abar_out, h->stream, t0, t1); });
     if (e == hipSuccess && multi) e = timed_launch(h, MD_K_LOGITS, [&] {
         return md::launch_logits(h->dm, h->v, h->sc, q, h->logits_blocks, h->stream); });
     // Sessions of at most kFoldChunks chunks: the mass kernel works out the

@@ -57,8 +57,6 @@ struct AttendDims {
     int aligned;
     int Gq, Wn;   // window (WN instantiations): query heads per KV head and window
                   // queries; G above counts the MFMA columns, Gq * Wn
-    int rg;       // row groups (RS instantiations): a unit covers one of rg
-                  // consecutive ranges of the L * Hkv rows; 1 = every row
 };
 
 struct AttendArgs {
@@ -88,6 +86,7 @@ struct AttendArgs {
     const int32_t* t_ins;         // window: insertion steps, for the causal mask
     int32_t* valid;               // [S] cleared for a session whose step is void
     unsigned long long* upart;    // row groups: [units][T] tagged partial masses
+    const int32_t* rgs;           // [S] row groups of each session's units (1: every row)
 };
 
 // LDS row stride (floats) of a head's values: W waves of KT tiles
@@ -137,16 +136,6 @@ __device__ __forceinline__ Lds carve(unsigned char* smem, int G, int W, int KT) 
     return l;
 }
 
-// Workgroup meeting point for LDS hand-offs.  A wave's LDS writes are done
-// once lgkmcnt is zero; the barrier carries no fence, so the waves' global
-// loads stay in flight across it.  The empty asm statements keep the
-// compiler from moving memory accesses over the barrier.
-__device__ __forceinline__ void lds_sync() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // Time limits, in ticks of the 100 MHz real-time counter.
 constexpr uint64_t kGlobalWaitTicks = 5000000ull;    // 50 ms for one row's statistics
 constexpr uint64_t kUnitTicks = 100000000ull;        // 1 s: a unit stops waiting after this
@@ -193,8 +182,8 @@ struct Unit {
     int s, j, ntok, nt_s, nu, us;
     uint64_t deadline;   // real-time tick after which the unit stops waiting
     int nl_s;            // region-aligned pages: the session's tokens |K_t| (nt_s counts holes too)
-    // row groups (RS): the unit covers rows [r0, r1) of group grp of rg; nu,
-    // j and us count the units of that group, ubase is the session's first
+    // row groups: the unit covers rows [r0, r1) of group grp of rg; nu, j
+    // and us count the units of that group, ubase is the session's first
     // unit (group 0)
     int r0, r1, grp, rg, ubase;
 };
@@ -212,13 +201,13 @@ __device__ __forceinline__ int qrow0(const AttendDims& dm, int r) { return r * d
 // decode queries (column c of a row is window query c / Gq, head c % Gq, and
 // a causal mask keeps each query to the tokens inserted by its step);
 // separate instantiations keep the plain kernel's register budget.
-// RS = row groups: the unit walks only its group's rows, and the groups'
-// partial masses meet in the unit of group 0, which alone finishes the
-// tokens (the plain instantiations walk every row).
+// With row groups (un.rg > 1) the unit walks only its group's rows, and the
+// groups' partial masses meet in the unit of group 0, which alone finishes
+// the tokens.
 // next_box (lane mode, the lane's first workgroup; else NULL): the lane's
 // next pass is claimed with claim_lane and cap once the unit's rows are
 // done, and published there.
-template <int W, int NH, int KT, bool AL, bool QT, bool WN, bool RS>
+template <int W, int NH, int KT, bool AL, bool QT, bool WN>
 __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendArgs& a, const Lds& sm,
                                             const Unit& un, int wv, int lane, uint32_t tag, int claim_lane,
                                             int cap, unsigned long long* next_box) {
@@ -234,8 +223,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     const int wtok0 = wv * 16 * KT;       // unit-local token of this wave's first tile
     bool dead = false;                    // a wait of this wave ran out: stop waiting
     // the unit's rows [r_beg, r_end)
-    const int r_beg = RS ? un.r0 : 0;
-    const int r_end = RS ? un.r1 : dm.LHkv;
+    const int r_beg = un.r0, r_end = un.r1;
 
     // lane i < KT: slot (physical page * P + offset) of tile i's first token
     int myslot = 0;
@@ -387,7 +375,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // Rows this unit leads are j, j + nu, j + 2 nu, ...: lead_next is the
     // next one to request, lead_now says whether the previous request was
     // this unit's (both advance once per iteration).
-    int lead_next = RS ? r_beg + ((un.j - r_beg) % un.nu + un.nu) % un.nu : un.j;
+    int lead_next = r_beg + ((un.j - r_beg) % un.nu + un.nu) % un.nu;
     bool lead_now = false;
     // Re-read until every active lane's words carry the step's tag (bounded).
     auto await_tags = [&](auto&& ready, auto&& reload) {
@@ -727,57 +715,55 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // masses to the unit of group 0 (same tokens) as tagged words, a NaN
     // payload marking a void step; that unit adds them in group order and
     // finishes the tokens alone.
-    if constexpr (RS) {
-        if (un.rg > 1) {
-            const bool void_here = *sm.vflag != 0;
-            unsigned long long* pbase = a.upart + (size_t)(un.ubase + un.j) * kT + wtok0 + lane;
-            const size_t gstride = (size_t)un.nu * kT;   // the words of one group's units
-            if (un.grp != 0) {
+    if (un.rg > 1) {
+        const bool void_here = *sm.vflag != 0;
+        unsigned long long* pbase = a.upart + (size_t)(un.ubase + un.j) * kT + wtok0 + lane;
+        const size_t gstride = (size_t)un.nu * kT;   // the words of one group's units
+        if (un.grp != 0) {
 #pragma unroll
-                for (int k = 0; k < kTok; ++k)
-                    __hip_atomic_store(pbase + un.grp * gstride + 64 * k,
-                                       tag_hi | (void_here ? 0x7fc00000u : __float_as_uint(acc[k])),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (void_here && threadIdx.x == 0) a.valid[un.s] = 0;
-                return;
-            }
-            if (!void_here) {
-                unsigned long long pw[kMaxRowGroups - 1][kTok];
-                auto load_parts = [&] {
-#pragma unroll
-                    for (int g2 = 1; g2 < kMaxRowGroups; ++g2)
-#pragma unroll
-                        for (int k = 0; k < kTok; ++k)
-                            pw[g2 - 1][k] = g2 < un.rg ? __hip_atomic_load(pbase + g2 * gstride + 64 * k, __ATOMIC_RELAXED,
-                                                                           __HIP_MEMORY_SCOPE_AGENT)
-                                                       : tag_hi;
-                };
-                load_parts();
-                await_tags(
-                    [&] {
-                        bool ok = true;
-#pragma unroll
-                        for (int g2 = 1; g2 < kMaxRowGroups; ++g2)
-#pragma unroll
-                            for (int k = 0; k < kTok; ++k) ok &= tag_ok(pw[g2 - 1][k]);
-                        return ok;
-                    },
-                    load_parts);
-                bool bad = false;
+            for (int k = 0; k < kTok; ++k)
+                __hip_atomic_store(pbase + un.grp * gstride + 64 * k,
+                                   tag_hi | (void_here ? 0x7fc00000u : __float_as_uint(acc[k])),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (void_here && threadIdx.x == 0) a.valid[un.s] = 0;
+            return;
+        }
+        if (!void_here) {
+            unsigned long long pw[kMaxRowGroups - 1][kTok];
+            auto load_parts = [&] {
 #pragma unroll
                 for (int g2 = 1; g2 < kMaxRowGroups; ++g2)
 #pragma unroll
-                    for (int k = 0; k < kTok; ++k) {
-                        if (g2 < un.rg) {
-                            const float pv = __uint_as_float((uint32_t)pw[g2 - 1][k]);
-                            bad |= pv != pv;
-                            acc[k] += pv;
-                        }
+                    for (int k = 0; k < kTok; ++k)
+                        pw[g2 - 1][k] = g2 < un.rg ? __hip_atomic_load(pbase + g2 * gstride + 64 * k, __ATOMIC_RELAXED,
+                                                                       __HIP_MEMORY_SCOPE_AGENT)
+                                                   : tag_hi;
+            };
+            load_parts();
+            await_tags(
+                [&] {
+                    bool ok = true;
+#pragma unroll
+                    for (int g2 = 1; g2 < kMaxRowGroups; ++g2)
+#pragma unroll
+                        for (int k = 0; k < kTok; ++k) ok &= tag_ok(pw[g2 - 1][k]);
+                    return ok;
+                },
+                load_parts);
+            bool bad = false;
+#pragma unroll
+            for (int g2 = 1; g2 < kMaxRowGroups; ++g2)
+#pragma unroll
+                for (int k = 0; k < kTok; ++k) {
+                    if (g2 < un.rg) {
+                        const float pv = __uint_as_float((uint32_t)pw[g2 - 1][k]);
+                        bad |= pv != pv;
+                        acc[k] += pv;
                     }
-                if (bad) *sm.vflag = 1;
-            }
-            lds_sync();   // every wave sees the unit's void flag
+                }
+            if (bad) *sm.vflag = 1;
         }
+        lds_sync();   // every wave sees the unit's void flag
     }
 
     // ---- Eq. 2 and Eq. 3 for this wave's tokens, then their retention
@@ -934,7 +920,7 @@ __device__ void claim_sessions(const AttendArgs& a, int* xs, int lane_no, int ca
 // the whole register file.  (Workgroups that take a whole CU, with eight
 // waves or with eight tiles per wave, measured slower: the two workgroups'
 // row barriers fall at different times and fill each other's gaps.)
-template <int W, int NH, int KT, bool AL, bool QT, bool WN, bool RS>
+template <int W, int NH, int KT, bool AL, bool QT, bool WN>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(NH == 4 ? 1 : 2)))
 k_attend(AttendDims dm, AttendArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1026,24 +1012,22 @@ k_attend(AttendDims dm, AttendArgs a) {
         const int s = sb + count_at_most(a.ustart + sb, se - sb, u0 + w, xs + 2) - 1;
         Unit un;
         un.s = s;
-        un.us = a.ustart[s];
-        un.nu = a.ustart[s + 1] - un.us;
+        un.us = uni(a.ustart[s]);
+        un.nu = uni(a.ustart[s + 1]) - un.us;
         un.j = u0 + w - un.us;
-        if constexpr (RS) {
-            // the session's units are rg groups of nu / rg units, group g
-            // covering rows [g L Hkv / rg, (g + 1) L Hkv / rg)
-            const int rg = min(max(dm.rg, 1), kMaxRowGroups);
-            const int nut = max(un.nu / rg, 1);
-            if (un.nu != nut * rg && threadIdx.x == 0) atomicOr(a.status, kDevCorrupt);
-            un.rg = rg;
-            un.ubase = un.us;
-            un.grp = min(un.j / nut, rg - 1);
-            un.j -= un.grp * nut;
-            un.nu = nut;
-            un.us += un.grp * nut;
-            un.r0 = un.grp * dm.LHkv / rg;
-            un.r1 = (un.grp + 1) * dm.LHkv / rg;
-        }
+        // the session's units are rg groups of nu / rg units, group g
+        // covering rows [g L Hkv / rg, (g + 1) L Hkv / rg)
+        const int rg = min(max(uni(a.rgs[s]), 1), kMaxRowGroups);
+        const int nut = max(un.nu / rg, 1);
+        if (un.nu != nut * rg && threadIdx.x == 0) atomicOr(a.status, kDevCorrupt);
+        un.rg = rg;
+        un.ubase = un.us;
+        un.grp = min(un.j / nut, rg - 1);
+        un.j -= un.grp * nut;
+        un.nu = nut;
+        un.us += un.grp * nut;
+        un.r0 = un.grp * dm.LHkv / rg;
+        un.r1 = (un.grp + 1) * dm.LHkv / rg;
         un.nt_s = a.n_tokens[s];
         un.nl_s = AL ? a.n_live[s] : 0;
         constexpr int kT = 16 * W * KT;
@@ -1055,7 +1039,7 @@ k_attend(AttendDims dm, AttendArgs a) {
         asm volatile("" : "+v"(lane));
         unsigned long long* next_box =
             (lanes && w == 0) ? a.lane_box + (size_t)lane_no * (dm.S + 1) + ps + 1 : nullptr;
-        attend_wave<W, NH, KT, AL, QT, WN, RS>(dm, a, sm, un, wv, lane, tag, lane_no, cap, next_box);
+        attend_wave<W, NH, KT, AL, QT, WN>(dm, a, sm, un, wv, lane, tag, lane_no, cap, next_box);
     }
 }
 
@@ -1068,24 +1052,22 @@ size_t attend_lds_bytes(int G) {
 }
 
 namespace {
-template <bool AL, bool QT, bool WN, bool RS = false>
+template <bool AL, bool QT, bool WN>
 const void* attend_for(int G) {
-    if (G <= 4) return reinterpret_cast<const void*>(&k_attend<4, 1, 4, AL, QT, WN, RS>);
-    if (G <= 8) return reinterpret_cast<const void*>(&k_attend<4, 2, 4, AL, QT, WN, RS>);
-    return reinterpret_cast<const void*>(&k_attend<4, 4, 4, AL, QT, WN, RS>);
+    if (G <= 4) return reinterpret_cast<const void*>(&k_attend<4, 1, 4, AL, QT, WN>);
+    if (G <= 8) return reinterpret_cast<const void*>(&k_attend<4, 2, 4, AL, QT, WN>);
+    return reinterpret_cast<const void*>(&k_attend<4, 4, 4, AL, QT, WN>);
 }
 }  // namespace
 
-// G: MFMA columns (query heads per KV head times window queries).  Row
-// groups run only on plain pages in full precision with one query.
-const void* attend_kernel(int G, int aligned, int quant, int window, int row_groups) {
+// G: MFMA columns (query heads per KV head times window queries).
+const void* attend_kernel(int G, int aligned, int quant, int window) {
     if (window > 1) {
         if (aligned) return quant ? attend_for<true, true, true>(G) : attend_for<true, false, true>(G);
         return quant ? attend_for<false, true, true>(G) : attend_for<false, false, true>(G);
     }
     if (aligned) return quant ? attend_for<true, true, false>(G) : attend_for<true, false, false>(G);
-    if (quant) return attend_for<false, true, false>(G);
-    return row_groups > 1 ? attend_for<false, false, false, true>(G) : attend_for<false, false, false>(G);
+    return quant ? attend_for<false, true, false>(G) : attend_for<false, false, false>(G);
 }
 
 // The grid as one launch: cooperative (the runtime keeps the device to it)
@@ -1093,9 +1075,9 @@ const void* attend_kernel(int G, int aligned, int quant, int window, int row_gro
 // less per step; residency is checked at init with the same launch kind).
 // With an event pair (t0, t1), an ordinary launch records the events with
 // the kernel's dispatch itself.
-static hipError_t launch_grid(const Dims& dm, int n_wg, int rg, void** args, hipStream_t st, hipEvent_t t0 = nullptr,
+static hipError_t launch_grid(const Dims& dm, int n_wg, void** args, hipStream_t st, hipEvent_t t0 = nullptr,
                               hipEvent_t t1 = nullptr) {
-    const void* fn = attend_kernel(dm.G * dm.W, dm.aligned, dm.quant, dm.W, rg);
+    const void* fn = attend_kernel(dm.G * dm.W, dm.aligned, dm.quant, dm.W);
     const dim3 grid(n_wg), block(attend_threads(dm.G * dm.W));
     const unsigned lds = (unsigned)attend_lds_bytes(dm.G * dm.W);
     if (dm.coop) return hipLaunchCooperativeKernel(fn, grid, block, args, lds, st);
@@ -1104,18 +1086,18 @@ static hipError_t launch_grid(const Dims& dm, int n_wg, int rg, void** args, hip
 }
 
 hipError_t launch_attend(const Dims& dm, const View& v, const Scratch& sc, const float* q, float* abar_out,
-                         int rg, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
+                         hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
     AttendDims ad{dm.L, dm.Hq, dm.Hkv, dm.G * dm.W, dm.P, dm.Pshift, dm.MP, dm.NP, dm.R, dm.LHkv,
                   dm.wg_per_cu, dm.n_wg / dm.wg_per_cu, dm.S, dm.n_regions, dm.norm_attn, dm.pin_mask,
-                  dm.rho, dm.tau_scale, dm.alpha, dm.aligned, dm.G, dm.W, rg};
+                  dm.rho, dm.tau_scale, dm.alpha, dm.aligned, dm.G, dm.W};
     AttendArgs aa{v.k_pool, v.page_table, v.n_tokens, v.clock, v.region, v.b, v.lam, v.imp, v.t_ref,
                   sc.pscore, q, abar_out, sc.ustart, sc.plan, sc.epoch, sc.claim, sc.lane_box, sc.ustat,
-                  sc.unorm, sc.status, nullptr, v.n_live, v.page_format, v.t_ins, sc.valid, sc.upart};
+                  sc.unorm, sc.status, nullptr, v.n_live, v.page_format, v.t_ins, sc.valid, sc.upart, sc.rgs};
     void* args[] = {&ad, &aa};
-    return launch_grid(dm, dm.n_wg, rg, args, st, t0, t1);
+    return launch_grid(dm, dm.n_wg, args, st, t0, t1);
 }
 
-hipError_t launch_attend_check(const Dims& dm, int32_t* probe, int n_wg, int rg, hipStream_t st) {
+hipError_t launch_attend_check(const Dims& dm, int32_t* probe, int n_wg, hipStream_t st) {
     AttendDims ad{};
     AttendArgs aa{};
     aa.probe = probe;
@@ -1123,7 +1105,7 @@ hipError_t launch_attend_check(const Dims& dm, int32_t* probe, int n_wg, int rg,
     if (e == hipSuccess) e = hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(probe + 1), 1 << 30, 1, st);
     if (e != hipSuccess) return e;
     void* args[] = {&ad, &aa};
-    return launch_grid(dm, n_wg, rg, args, st);
+    return launch_grid(dm, n_wg, args, st);
 }
 
 }  // namespace md

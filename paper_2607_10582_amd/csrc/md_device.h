@@ -72,12 +72,25 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// Workgroup meeting point for hand-offs through LDS.  A wave's LDS accesses
+// are done once lgkmcnt is zero; unlike __syncthreads the barrier does not
+// wait for the wave's global loads and stores, so they stay in flight across
+// it (a store not yet acknowledged costs a __syncthreads about a
+// microsecond).  It orders no global memory.  The empty asm statements keep
+// the compiler from moving memory accesses over the barrier.
+__device__ __forceinline__ void lds_sync() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // N exclusive block-wide scans side by side (any multiple of 64 threads up
 // to 1024; lds: 17 N ints).  Each wave scans its lanes (DPP) and publishes
 // its total; after one barrier every wave scans the (at most 16) wave totals
 // itself, so no thread walks them serially.  Ends with a barrier, after
-// which lds may be reused.
-template <int N>
+// which lds may be reused: __syncthreads, or with LdsOnly lds_sync, for a
+// caller that needs no global access ordered by it.
+template <int N, bool LdsOnly = false>
 __device__ inline void block_exclusive_scan_n(const int (&v)[N], int* lds, int (&ex)[N], int (&total)[N]) {
     const int lane = lane_id(), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
     int incl[N];
@@ -86,7 +99,7 @@ __device__ inline void block_exclusive_scan_n(const int (&v)[N], int* lds, int (
     if (lane == 63)
 #pragma unroll
         for (int k = 0; k < N; ++k) lds[17 * k + wid] = incl[k];
-    __syncthreads();
+    if constexpr (LdsOnly) lds_sync(); else __syncthreads();
 #pragma unroll
     for (int k = 0; k < N; ++k) {
         const int t = wave_incl_sum(lane < nw ? lds[17 * k + lane] : 0);
@@ -94,7 +107,7 @@ __device__ inline void block_exclusive_scan_n(const int (&v)[N], int* lds, int (
         ex[k] = (wid > 0 ? before : 0) + incl[k] - v[k];
         total[k] = __builtin_amdgcn_readlane(t, nw - 1);
     }
-    __syncthreads();
+    if constexpr (LdsOnly) lds_sync(); else __syncthreads();
 }
 
 // Exclusive prefix of one int per thread across the whole block; *total is

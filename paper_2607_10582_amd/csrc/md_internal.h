@@ -22,7 +22,8 @@ constexpr int kPerThread = kMaxPages / kSelThreads;
 // wave's four tiles of 16 tokens) over every (layer, KV head) row.
 constexpr int kAttendPerCu = 2;   // at most two workgroups per CU
 inline int attend_threads(int) { return 256; }
-inline int attend_unit_tokens(int) { return 256; }
+constexpr int kUnitTokens = 256;
+inline int attend_unit_tokens(int) { return kUnitTokens; }
 constexpr int kConsumeLag = 7;   // rows a unit runs ahead of the row it normalises
 // Row groups: when a step's units fill less than half of the fused grid, each
 // unit may cover one of up to kMaxRowGroups ranges of the L * Hkv rows
@@ -30,6 +31,10 @@ constexpr int kConsumeLag = 7;   // rows a unit runs ahead of the row it normali
 // the unit of the first group.
 constexpr int kMaxRowGroups = 16;
 constexpr int kMinGroupRows = 8;
+// A last pass that fills only part of the grid: its sessions' units may
+// split down to this many rows (the append kernel plans it).  Below four
+// rows a unit is all prologue and drain.
+constexpr int kMinTailRows = 4;
 constexpr int kRowBufs = kConsumeLag + 1;       // rows of logits held in LDS
 
 constexpr int kFoldChunks = 16;    // multi-kernel path: sessions of at most 2,048 tokens fold their row statistics into the mass kernel
@@ -57,7 +62,8 @@ struct Dims {
     int lane_cap;  // units one lane of k_attend workgroups holds (one workgroup per CU)
     int T;         // tokens per fused unit (attend_unit_tokens(G))
     int U_cap;     // capacity of the per-step fused unit list
-    int rg_max;    // most row groups any step uses (1: none; sizes the partial masses)
+    int rg_max;    // most row groups of a step that splits every unit (1: none)
+    int tail;      // most row groups of the units of a step's last pass (1: never split)
     uint32_t pin_mask;
     float rho, alpha, tau_scale;
 };
@@ -112,6 +118,7 @@ struct Scratch {
     unsigned long long* ustat;  // [U_cap][R][2] tagged (max, sum) of each fused unit's rows
     unsigned long long* unorm;  // [S][R][2] tagged row normalisers (M, 1 / Lambda) of the fused sessions
     unsigned long long* upart;  // [U_cap][T] row groups: tagged partial masses of each unit's tokens
+    int32_t* rgs;          // [S] row groups of each session's fused units (1: every row)
     int32_t* chunks;       // [S] chunks per session (0 for a skipped session)
     int32_t* valid;        // [S] 1 while the session's step stands: its counters are
                            // consistent, its query finite and no wait of the fused
@@ -157,21 +164,19 @@ hipError_t launch_append(const Dims& dm, const View& v, const Scratch& sc,
 hipError_t launch_logits(const Dims& dm, const View& v, const Scratch& sc, const float* q,
                          int n_blocks, hipStream_t st);
 hipError_t launch_rowstats(const Dims& dm, const Scratch& sc, hipStream_t st);
-// rg: row groups, as given to the step's append.  t0, t1: when not NULL
-// (ordinary launches only), an event pair recorded by the kernel's dispatch
-// itself
+// t0, t1: when not NULL (ordinary launches only), an event pair recorded by
+// the kernel's dispatch itself
 hipError_t launch_attend(const Dims& dm, const View& v, const Scratch& sc, const float* q,
-                         float* abar_out, int rg, hipStream_t st, hipEvent_t t0 = nullptr,
+                         float* abar_out, hipStream_t st, hipEvent_t t0 = nullptr,
                          hipEvent_t t1 = nullptr);
 size_t attend_lds_bytes(int G);
 // the instantiation for G MFMA columns (heads per KV head x window), layout,
-// tier, window and row groups (> 1: the row-group instantiation)
-const void* attend_kernel(int G, int aligned, int quant, int window, int row_groups);
-// Launch the fused kernel (the instantiation for rg row groups) in check
-// mode with n_wg workgroups: every wave waits (bounded, ~20 ms) until all
-// workgroups have arrived; probe[1] receives the fewest arrivals any
-// workgroup saw (probe: 2 device ints).
-hipError_t launch_attend_check(const Dims& dm, int32_t* probe, int n_wg, int rg, hipStream_t st);
+// tier and window
+const void* attend_kernel(int G, int aligned, int quant, int window);
+// Launch the fused kernel in check mode with n_wg workgroups: every wave
+// waits (bounded, ~20 ms) until all workgroups have arrived; probe[1]
+// receives the fewest arrivals any workgroup saw (probe: 2 device ints).
+hipError_t launch_attend_check(const Dims& dm, int32_t* probe, int n_wg, hipStream_t st);
 // fold: the mass kernel works out the row statistics itself (no
 // launch_rowstats before it; sessions of at most kFoldChunks chunks).  It
 // also writes the page scores of the sessions it observes.

@@ -89,6 +89,61 @@ __device__ __forceinline__ unsigned long long append_word(uint32_t tag, bool bad
            (unsigned long long)(nt & 0xFFFFF);
 }
 
+// Fused units of a session of n token slots.
+__device__ __forceinline__ int unit_count(int n) { return (n + kUnitTokens - 1) / kUnitTokens; }
+
+// Lane mode, sessions left after the lanes' first passes: the sessions
+// [tf, te) whose units split into tg row groups (tg = 1: none).
+struct LaneTail {
+    int tf, te, tg;
+};
+
+// One wave, every lane with the same arguments: plays the lanes' claims on
+// the sessions [f, e) through, lane 0 from the front, lane 1 from the back,
+// in turn (whole sessions of at most cap units, at most `most` of them), and
+// splits what no longer fills more than one lane pass.  pre[0 .. S) is the
+// prefix of the sessions' units, tot their sum.
+__device__ __forceinline__ LaneTail plan_tail(const int* pre, int S, int tot, int f, int e, int cap, int most,
+                                              int tail) {
+    const int lane = lane_id();
+    auto at = [&](int s) { return s < S ? pre[s] : tot; };
+    // sessions a claim takes from [f, e), from its front or its back, of
+    // units times g
+    auto claim = [&](int f, int e, bool front, int g) {
+        const int n = min(e - f, most);
+        int k = 0;
+        for (int c = 0; c < n; c += 64) {
+            const int i = c + lane + 1;   // i sessions taken
+            const bool fits = i <= n && g * (front ? at(f + i) - at(f) : at(e) - at(e - i)) <= cap;
+            const int m = __popcll(__ballot(fits));
+            k += m;
+            if (m < 64) break;
+        }
+        return uni(k);
+    };
+    for (int c = 0; f < e; ++c) {
+        const int rem = uni(at(e) - at(f));
+        if (rem <= cap) {
+            // as many row groups as two claims (one per lane) hold
+            int um = 0;
+            for (int s = f + lane; s < e; s += 64) um = max(um, at(s + 1) - at(s));
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) um = max(um, __shfl_xor(um, o));
+            int g = uni(min(tail, min(2 * cap / max(rem, 1), cap / max(um, 1))));
+            for (; g > 1; --g) {
+                const int k = claim(f, e, true, g);
+                if (f + k == e || f + k + claim(f + k, e, true, g) == e) break;
+            }
+            return LaneTail{f, e, max(g, 1)};
+        }
+        const bool front = (c & 1) == 0;
+        const int k = claim(f, e, front, 1);
+        if (k == 0) break;   // cannot happen: every session fits half a lane
+        if (front) f += k; else e -= k;
+    }
+    return LaneTail{S, S, 1};
+}
+
 __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
                                                 const uint16_t* __restrict__ new_k,
                                                 const uint8_t* __restrict__ new_region, int fused,
@@ -132,13 +187,13 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
     if (new_k != nullptr)
         for (int s2 = threadIdx.x; s2 < s; s2 += blockDim.x) rank_mine += opens_page(dm, v, s2, new_region) ? 1 : 0;
     if (threadIdx.x == 0 && np > 0 && np <= dm.MP) last_p = v.page_table[(size_t)s * dm.MP + np - 1];
-    __syncthreads();
+    lds_sync();
     if (new_k != nullptr) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) rank_mine += __shfl_xor(rank_mine, o);
         if (lane_id() == 0 && rank_mine > 0) atomicAdd(&sh_rank, rank_mine);
     }
-    __syncthreads();
+    lds_sync();
     if (threadIdx.x == 0) {
         // Every load first, then the stores: a wait for a load also waits
         // for the stores issued before it.
@@ -220,7 +275,7 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
         __hip_atomic_store(sc.app_word + s, append_word(tag, bad, appended, np, nt), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
+    lds_sync();
     const int phys = sh_phys;
     if (phys >= 0) {
         // piece b of row r goes to its 16-token block's [b][slot mod 16] place
@@ -252,7 +307,10 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
     __shared__ int s_live[kMaxSessions];   // live tokens (with region-aligned pages, holes left out)
     __shared__ int s_pass[kMaxSessions];   // fused pass of the session, -1 on the spill path
     __shared__ int s_pb[kMaxSessions], s_pe[kMaxSessions], s_pl[kMaxSessions];   // pass mode: sessions, units
-    __syncthreads();
+    __shared__ int s_rg[kMaxSessions];     // row groups of the session's units
+    __shared__ LaneTail sh_lt;
+    __shared__ int sh_f0, sh_e1;
+    lds_sync();
     for (int s2 = threadIdx.x; s2 < dm.S; s2 += blockDim.x) {
         // loads before the stores (a wait for a load also waits for them)
         const int live0 = dm.aligned ? v.n_live[s2] : 0;
@@ -282,7 +340,7 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
         s_live[s2] = (ok && nt > 0) ? live : 0;
         s_pass[s2] = -1;
     }
-    __syncthreads();
+    lds_sync();
     // Entries off the free list: one per session that wants a page, as every
     // block ranked them from the counts before the append (sh_rank counts
     // the other sessions here), whether or not its word arrived in time; a
@@ -299,18 +357,19 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
     // and let each workgroup start its next unit as soon as it is done.
     __shared__ int s_lane_ok;
     if (threadIdx.x == 0) s_lane_ok = fused && dm.wg_per_cu >= 2;
-    __syncthreads();
-    // With row groups a session's units are rg groups of its token units.
+    lds_sync();
+    // A session's units are its token units times its row groups (the step's
+    // rg, or more in a last pass that would fill little of the grid).
     if (fused) {
         for (int s2 = threadIdx.x; s2 < dm.S; s2 += blockDim.x) {
-            const int u = (s_n[s2] + dm.T - 1) / dm.T * rg;
+            const int u = unit_count(s_n[s2]) * rg;
+            s_rg[s2] = rg;
             if (2 * u > dm.lane_cap) atomicExch(&s_lane_ok, 0);
             if (u <= dm.n_wg) s_pass[s2] = 0;
         }
+        lds_sync();
     }
-    __syncthreads();
     const bool lane_mode = fused && s_lane_ok;
-    __shared__ int sh_f0, sh_e1;
     if (threadIdx.x == 0) {
         sh_f0 = min(dm.S, (int)blockDim.x);
         sh_e1 = max(0, dm.S - (int)blockDim.x);
@@ -321,14 +380,15 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
         // so all of them run in the same pass).  A session larger than a
         // whole pass takes the spill path.  (The lane plan follows the work
         // lists below.)
-        // Then neighbouring passes are evened out from the back: greedy
-        // packing can leave the last pass nearly empty (16 sessions of 129
-        // units give five passes of three and one of one), and a pass of few
-        // units streams at a fraction of the bandwidth (a quarter of the grid
-        // reads at about 2.5 TB/s, half of it at about 6.4), so the previous
-        // pass's last sessions move into the next one while that lowers the
-        // larger of the two passes' units.
-        auto units = [&](int s2) { return (s_n[s2] + dm.T - 1) / dm.T * rg; };
+        // A pass of few units streams at a fraction of the bandwidth (a
+        // quarter of the grid reads at about 2.5 TB/s, half of it at about
+        // 6.4).  Greedy packing leaves the shortage to the last pass, whose
+        // units then split by rows until they fill the grid: 33 units of 56
+        // rows alone took 130 us, as 15 groups of 4 rows about 40 us.
+        // Without row groups neighbouring passes are evened out from the
+        // back instead: the previous pass's last sessions move into the next
+        // one while that lowers the larger of the two passes' units.
+        auto units = [&](int s2) { return unit_count(s_n[s2]) * rg; };
         for (int s2 = 0; s2 < dm.S; ++s2) s_pass[s2] = -1;
         int np = 0, s0 = 0;
         while (s0 < dm.S) {
@@ -349,14 +409,21 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
             ++np;
             s0 = e;
         }
-        for (int p = np - 1; p >= 1; --p) {
-            while (s_pe[p - 1] == s_pb[p] && s_pe[p - 1] - s_pb[p - 1] > 1) {
-                const int u = units(s_pe[p - 1] - 1);
-                if (s_pl[p] + u > dm.n_wg || s_pl[p] + u >= s_pl[p - 1]) break;
-                s_pl[p - 1] -= u;
-                s_pl[p] += u;
-                s_pe[p - 1] -= 1;
-                s_pb[p] -= 1;
+        if (dm.tail > 1 && rg == 1) {
+            const int p = np - 1;
+            const int g = np > 1 ? min(dm.tail, dm.n_wg / max(s_pl[p], 1)) : 1;
+            if (g > 1)
+                for (int s2 = s_pb[p]; s2 < s_pe[p]; ++s2) s_rg[s2] = g;
+        } else {
+            for (int p = np - 1; p >= 1; --p) {
+                while (s_pe[p - 1] == s_pb[p] && s_pe[p - 1] - s_pb[p - 1] > 1) {
+                    const int u = units(s_pe[p - 1] - 1);
+                    if (s_pl[p] + u > dm.n_wg || s_pl[p] + u >= s_pl[p - 1]) break;
+                    s_pl[p - 1] -= u;
+                    s_pl[p] += u;
+                    s_pe[p - 1] -= 1;
+                    s_pb[p] -= 1;
+                }
             }
         }
         for (int p = 0; p < np; ++p) {
@@ -368,7 +435,7 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
         sc.plan[0] = np;
         *sc.epoch = ep0 + 1;
     }
-    __syncthreads();
+    lds_sync();
     // Work lists: fused units; attention items, chunks and mass tiles of the
     // spill path; score tiles for every session.
     int uu[4], it[4], ti[4], si[4];
@@ -383,7 +450,7 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
             const bool spill = ps < 0;
             const int ch = spill ? (nt + kChunk - 1) / kChunk : 0;
             sc.chunks[s2] = ch;
-            uu[k] = spill ? 0 : (nt + dm.T - 1) / dm.T * rg;
+            uu[k] = spill ? 0 : unit_count(nt) * s_rg[s2];
             it[k] = ch * dm.LHkv;
             ti[k] = spill ? (nt + kTile - 1) / kTile : 0;
             si[k] = (nt + kTile - 1) / kTile;
@@ -396,7 +463,7 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
     }
     const int mine[5] = {my_units, my_items, my_tiles, my_stiles, my_tokens};
     int ex[5], tot[5];
-    block_exclusive_scan_n<5>(mine, lds, ex, tot);
+    block_exclusive_scan_n<5, true>(mine, lds, ex, tot);
     int ex_u = ex[0], ex_i = ex[1], ex_t = ex[2], ex_s = ex[3];
     const int tot_u = tot[0], tot_i = tot[1], tot_t = tot[2], tot_s = tot[3], tot_n = tot[4];
     // Lane mode: the first pass of each lane, claimed here: lane 0 the
@@ -408,14 +475,15 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
     // suffix count does (both counts are monotone), each found by the one
     // thread that sees the crossing.
     const int cap = dm.lane_cap;
+    int* pre = s_pb;   // units before each session
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int s2 = threadIdx.x * 4 + k;
         if (s2 < dm.S) {
-            sc.ustart[s2] = ex_u;
             sc.item_prefix[s2] = ex_i;
             sc.tile_prefix[s2] = ex_t;
             sc.score_prefix[s2] = ex_s;
+            pre[s2] = ex_u;
             if (lane_mode) {
                 const int incl = ex_u + uu[k];
                 if (s2 < (int)blockDim.x && ex_u <= cap && cap < incl) atomicMin(&sh_f0, s2);
@@ -427,23 +495,63 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
         ex_t += ti[k];
         ex_s += si[k];
     }
-    if (lane_mode) __syncthreads();
+    int f0 = 0, e1 = 0, all_u = tot_u;
+    bool single = false;
+    LaneTail lt{dm.S, dm.S, 1};
+    if (fused) lds_sync();
+    if (lane_mode) {
+        f0 = sh_f0;
+        e1 = max(sh_e1, f0);
+        // Sessions left for later claims.  If all units fit the grid at once
+        // and only the cut into whole sessions per lane leaves some, one pass
+        // over the whole grid takes them all.  Otherwise the last ones, when
+        // they would run alone on part of a lane, split by rows so that they
+        // fill up to both: one 32-unit session of 56 rows ran alone for 130 us
+        // of a 400 us launch, in seven groups about 45 us, most of it beside
+        // the other lane's last units (16 sessions at an 8,192-token budget:
+        // 374 to 323 us a step; 64 sessions, 439,000 tokens: 1,389 to 1,280).
+        single = f0 < e1 && tot_u <= 2 * cap;
+        if (f0 < e1 && !single && rg == 1 && dm.tail > 1) {
+            if (threadIdx.x < 64) {
+                const LaneTail lt = plan_tail(pre, dm.S, tot_u, f0, e1, cap, (int)blockDim.x, dm.tail);
+                if (threadIdx.x == 0) sh_lt = lt;
+            }
+            lds_sync();
+            lt = sh_lt;
+        }
+    }
+    if (fused) {
+        const int u0 = lt.tg > 1 ? pre[lt.tf] : 0;
+        const int more = lt.tg > 1 ? (lt.tg - 1) * ((lt.te < dm.S ? pre[lt.te] : tot_u) - u0) : 0;
+        for (int s2 = threadIdx.x; s2 < dm.S; s2 += blockDim.x) {
+            const bool in = s2 >= lt.tf && s2 < lt.te;
+            sc.ustart[s2] = in ? u0 + (pre[s2] - u0) * lt.tg : pre[s2] + (s2 >= lt.te ? more : 0);
+            sc.rgs[s2] = in ? lt.tg : s_rg[s2];
+        }
+        all_u += more;
+    }
     if (threadIdx.x == 0) {
         if (lane_mode) {
-            const int f0 = sh_f0, e1 = max(sh_e1, f0);
             const int ep = ep0 + 1;
-            sc.plan[0] = -1;
             *sc.epoch = ep;
-            const unsigned long long tag = (unsigned long long)(uint32_t)ep << 32;
-            sc.lane_box[0] = tag | ((unsigned long long)0 << 16) | (unsigned long long)f0;
-            sc.lane_box[dm.S + 1] = tag | ((unsigned long long)e1 << 16) | (unsigned long long)dm.S;
-            *sc.claim = ((unsigned long long)(uint32_t)f0 << 32) | (uint32_t)e1;
+            if (single) {
+                sc.plan[0] = 1;
+                sc.plan[1] = dm.T;
+                sc.plan[2] = 0;
+                sc.plan[3] = dm.S;
+            } else {
+                sc.plan[0] = -1;
+                const unsigned long long tag = (unsigned long long)(uint32_t)ep << 32;
+                sc.lane_box[0] = tag | ((unsigned long long)0 << 16) | (unsigned long long)f0;
+                sc.lane_box[dm.S + 1] = tag | ((unsigned long long)e1 << 16) | (unsigned long long)dm.S;
+                *sc.claim = ((unsigned long long)(uint32_t)f0 << 32) | (uint32_t)e1;
+            }
         }
-        if (tot_u > dm.U_cap) {            // cannot happen for consistent counters
+        if (all_u > dm.U_cap) {            // cannot happen for consistent counters
             atomicOr(sc.status, kDevCorrupt);
             sc.plan[0] = 0;
         }
-        sc.ustart[dm.S] = tot_u;
+        sc.ustart[dm.S] = all_u;
         sc.item_prefix[dm.S] = tot_i;
         sc.tile_prefix[dm.S] = tot_t;
         sc.score_prefix[dm.S] = tot_s;
@@ -1717,13 +1825,13 @@ size_t scratch_bytes(const Dims& dm) {
     n += align256(spill * dm.S * dm.R * dm.max_chunks * sizeof(float2));
     n += align256((size_t)dm.S * dm.R * sizeof(float2));
     n += align256((size_t)dm.S * dm.MP * sizeof(float));
-    n += 7 * align256((size_t)(dm.S + 1) * sizeof(int32_t));
+    n += 8 * align256((size_t)(dm.S + 1) * sizeof(int32_t));
     n += align256((size_t)(1 + 3 * (dm.S + 1)) * sizeof(int32_t));
     n += align256(sizeof(int32_t));
     n += align256((1 + (size_t)kAttendPerCu * (dm.S + 1)) * sizeof(unsigned long long));
     n += align256((size_t)dm.R * dm.U_cap * 2 * sizeof(unsigned long long));
     n += align256((dm.fused ? (size_t)dm.S * dm.R : 0) * 2 * sizeof(unsigned long long));
-    n += align256((dm.rg_max > 1 ? (size_t)dm.U_cap * dm.T : 0) * sizeof(unsigned long long));
+    n += align256((dm.rg_max > 1 || dm.tail > 1 ? (size_t)dm.U_cap * dm.T : 0) * sizeof(unsigned long long));
     n += align256(4 * sizeof(int32_t));
     n += align256(9 * sizeof(unsigned long long));
     n += 3 * align256((size_t)dm.S * sizeof(unsigned long long));
@@ -1751,6 +1859,7 @@ void scratch_carve(const Dims& dm, void* base, Scratch* sc) {
     sc->freed = reinterpret_cast<int32_t*>(take((size_t)(dm.S + 1) * sizeof(int32_t)));
     sc->score_prefix = reinterpret_cast<int32_t*>(take((size_t)(dm.S + 1) * sizeof(int32_t)));
     sc->ustart = reinterpret_cast<int32_t*>(take((size_t)(dm.S + 1) * sizeof(int32_t)));
+    sc->rgs = reinterpret_cast<int32_t*>(take((size_t)(dm.S + 1) * sizeof(int32_t)));
     sc->plan = reinterpret_cast<int32_t*>(take((size_t)(1 + 3 * (dm.S + 1)) * sizeof(int32_t)));
     sc->epoch = reinterpret_cast<int32_t*>(take(sizeof(int32_t)));
     sc->claim = reinterpret_cast<unsigned long long*>(
@@ -1761,7 +1870,7 @@ void scratch_carve(const Dims& dm, void* base, Scratch* sc) {
     sc->unorm = reinterpret_cast<unsigned long long*>(
         take((dm.fused ? (size_t)dm.S * dm.R : 0) * 2 * sizeof(unsigned long long)));
     sc->upart = reinterpret_cast<unsigned long long*>(
-        take((dm.rg_max > 1 ? (size_t)dm.U_cap * dm.T : 0) * sizeof(unsigned long long)));
+        take((dm.rg_max > 1 || dm.tail > 1 ? (size_t)dm.U_cap * dm.T : 0) * sizeof(unsigned long long)));
     int32_t* words = reinterpret_cast<int32_t*>(take(4 * sizeof(int32_t)));
     sc->status = words;      // the warning word follows the status word (read together)
     sc->warn = words + 1;

@@ -1,0 +1,94 @@
+"""Row groups of a step's last pass, through the C ABI on the device.
+
+When the units of a step need more than one pass over the fused grid and the
+last one would leave most of it idle, its sessions' units split by rows.  A
+step must not depend on that beyond rounding: the masses, refresh clocks,
+page scores and selections with and without row groups are compared on every
+plan (lane passes with a rest, one pass instead of lane passes with a rest,
+passes of long sessions) and for every layout and tier.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2607_10582_amd import binding as B
+from paper_2607_10582_amd.cache import MemDecay, PagedCache
+
+from harness import REL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a ROCm device")
+    B.load_library()
+
+
+def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, quant=0.0):
+    """Two steps over sessions of `tokens` tokens; the same inputs for every
+    setting of row_groups.  Budgets keep every token, so slots line up."""
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    S = len(tokens)
+    # runs of 40 tokens: with region-aligned pages every third page is half full
+    regions = [np.repeat(1 + np.arange(-(-n // 40)) % 6, 40)[:n].astype(np.uint8) for n in tokens]
+    pages = [PagedCache.pages_for(r, P, aligned) for r in regions]
+    cache = PagedCache(L=L, Hq=Hq, Hkv=Hkv, d=128, P=P, S=S, max_pages=max(pages) + 4, n_phys=sum(pages) + 4 * S)
+    ids = np.random.default_rng(3).permutation(cache.n_phys)
+    at = 0
+    for s, n in enumerate(tokens):
+        keys = torch.randn((n, L, Hkv, 128), generator=gen, device="cuda").to(torch.bfloat16)
+        cache.load_session(s, keys, regions[s], ids[at:at + pages[s]], budget=2 * n, clock=n, region_aligned=aligned)
+        at += pages[s]
+    cache.set_free_pages(ids[at:])
+    md = MemDecay(cache, torch.full((S, 7), 0.5), torch.full((S, 7), 0.01), rho=0.9, alpha=1.0, tau_scale=2.0,
+                  pinned_mask=1, fused=True, window=window, region_aligned=aligned, quant_threshold=quant,
+                  row_groups=row_groups)
+    abar = torch.zeros((cache.n_phys, P), device="cuda")
+    out = []
+    for k in range(steps):
+        q = torch.randn((S, window, L, Hq, 128), generator=gen, device="cuda")
+        nk = torch.randn((S, L, Hkv, 128), generator=gen, device="cuda").to(torch.bfloat16)
+        reg = torch.full((S,), 1 + k, dtype=torch.uint8, device="cuda")
+        md.observe(k, q, nk, reg, abar_out=abar)
+        md.score()
+        md.select()
+        md.compact()
+        out.append([x.cpu().numpy().copy() for x in (abar, cache.importance, md.page_score, md.evict_count)])
+    assert md.device_status() == 0
+    cfg = md.kernel_config()
+    cfg["units"] = int(((cache.n_tokens + 255) // 256).sum())
+    md.close()
+    return out, cfg
+
+
+@pytest.mark.parametrize("label,tokens,L,Hq,Hkv,P,kw", [
+    # 17 sessions of 32 units: eight to a lane, one left, in four groups
+    ("lanes", [8100] * 17, 8, 12, 2, 16, {}),
+    # uneven sessions, several claims per lane, a rest of several sessions
+    ("lanes-uneven", [300 * (1 + (7 * s) % 29) for s in range(40)], 6, 8, 2, 64, {}),
+    # five of 100 units fit the grid, but not as two lanes of whole sessions
+    ("one-pass", [25500] * 5, 4, 8, 2, 16, {}),
+    # sessions of more than half a lane: three to a pass, one left
+    ("passes", [35800] * 4, 8, 16, 2, 16, {}),
+    ("heads-per-group-16", [8100] * 9, 8, 16, 1, 16, {}),
+    ("window", [8100] * 9, 8, 12, 2, 16, {"window": 2}),
+    ("aligned", [7000] * 17, 8, 12, 2, 16, {"aligned": True}),
+    ("quantised", [8100] * 17, 8, 12, 2, 16, {"quant": 10.0}),
+])
+def test_last_pass_in_row_groups_agrees_with_every_row(label, tokens, L, Hq, Hkv, P, kw):
+    a, ca = run(tokens, L, Hq, Hkv, P, True, **kw)
+    b, cb = run(tokens, L, Hq, Hkv, P, False, **kw)
+    assert ca["first_fused"] and not ca["spill"] and ca["first_row_groups"] == cb["first_row_groups"] == 1
+    n = ca["units"]
+    assert n > ca["workgroups"] or label == "one-pass"
+    for step, (x, y) in enumerate(zip(a, b)):
+        for u, v in zip(x[:3], y[:3]):
+            assert np.array_equal(np.isfinite(u), np.isfinite(v))
+            fin = np.isfinite(v)
+            np.testing.assert_allclose(u[fin], v[fin], rtol=REL, atol=1e-30, err_msg=f"{label} step {step}")
+        assert np.array_equal(x[3], y[3])
+    total = float(a[0][0].sum())
+    assert abs(total - len(tokens)) < 1e-3 * len(tokens)   # every session's masses add up to 1
+    print(f"[{label}] {n} units on {ca['workgroups']} workgroups ok", flush=True)
