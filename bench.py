@@ -272,18 +272,27 @@ def measure(w, W: int, K: int, dev, *, multi_kernel=False, calibrate=0, offload_
     # eviction) are counted on their own
     c_start = md.counters()
     first_end = torch.cuda.Event(enable_timing=True)
+    appends = 1
     for k in range(1, W + 1):
         ev[k - 1].record(stream)
+        if k > 1 and inputs[k - 1][0] is not None:
+            md.profile(("append",))
         run(k)
         if k == 1:
             first_end.record(stream)
             c_first = md.counters()
+        elif inputs[k - 1][0] is not None:
+            appends = md.profile_read("append")[1]
+            md.profile(())
     ev[W].record(stream)
     torch.cuda.synchronize(dev)
     c0 = md.counters()
     kcfg = md.kernel_config()
-    hot = "attend" if kcfg["steady_fused"] and not kcfg["spill"] else "logits"
-    log(f"kernel config {kcfg}; timing k_{hot}")
+    # the session kernel appends in its own launch (and is timed as "attend")
+    session = appends == 0
+    hot = "attend" if session or (kcfg["steady_fused"] and not kcfg["spill"]) else "logits"
+    hot_kernel = "rows" if session else hot
+    log(f"kernel config {kcfg}; timing k_{hot_kernel}")
     md.profile((hot,))
     q_tok0 = quantised_tokens(cache) if w.quant_threshold > 0 else 0
     if calibrate:
@@ -358,7 +367,7 @@ def measure(w, W: int, K: int, dev, *, multi_kernel=False, calibrate=0, offload_
     # switched on from the command line reads other bytes (its own profile
     # name carries the threshold)
     prof_name = w.name if w.quant_threshold == C.get(w.name).quant_threshold else f"{w.name}_quant{w.quant_threshold:g}"
-    traffic, traffic_src = load_traffic(hot, prof_name)
+    traffic, traffic_src = load_traffic(hot_kernel, prof_name)
     # whole step: K + per-token state (region 1, a 4+4, t_ref 4+4) + per-page
     # score and page-table entry + the queries
     step_bytes = scored * (kb + 17) + scored // w.P * 8 + K * q_bytes - q_saved
@@ -374,7 +383,7 @@ def measure(w, W: int, K: int, dev, *, multi_kernel=False, calibrate=0, offload_
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": achieved / PEAK_HBM_GBS, "traffic": traffic,
                      "traffic_source": None if traffic is None else os.path.relpath(traffic_src, ROOT),
-                     "kernel": f"k_{hot}", "launches": launches,
+                     "kernel": f"k_{hot_kernel}", "launches": launches,
                      "avg_launch_us": avg_launch_s * 1e6,
                      "algorithmic_bytes_per_launch": per_launch_bytes},
         "tokens_scored_per_step": scored / K,
@@ -395,7 +404,7 @@ def measure(w, W: int, K: int, dev, *, multi_kernel=False, calibrate=0, offload_
         "step_frac_of_peak": step_bytes / wall / 1e9 / PEAK_HBM_GBS,
         "observe_path": {"first": "fused" if kcfg["first_fused"] else "multi-kernel",
                          "first_row_groups": kcfg["first_row_groups"],
-                         "steady": "fused" if kcfg["steady_fused"] else "multi-kernel",
+                         "steady": "session" if session else "fused" if kcfg["steady_fused"] else "multi-kernel",
                          "steady_row_groups": kcfg["steady_row_groups"]},
     }
     if offload_pages > 0:

@@ -146,10 +146,12 @@ enum {
                                 /* hold the sessions.  With neither flag,       */
                                 /* md_init picks the path of the first observe  */
                                 /* and of the later ones from the cache's sizes */
-                                /* and budgets at init: the fused kernel walks  */
-                                /* the layers in order, so for small caches the */
-                                /* multi-kernel path, parallel over layers, is  */
-                                /* faster                                       */
+                                /* and budgets at init: the session kernel (a   */
+                                /* workgroup per session and range of rows) for */
+                                /* short sessions; else the fused kernel, which */
+                                /* walks the layers in order, or for small      */
+                                /* caches the multi-kernel path, parallel over  */
+                                /* layers                                       */
 #define MD_FLAG_NO_ROW_GROUPS 0x20 /* keep every fused unit on all L Hkv rows. */
                                 /* By default a step whose units would fill     */
                                 /* less than half of the fused kernel's grid    */
@@ -450,7 +452,11 @@ md_status md_read_counters(md_handle h, int64_t* out);
  * fused kernel's workgroups (all resident at once), out[4] 1 when the first
  * md_observe_step runs the fused kernel, out[5] 1 when the later ones do,
  * out[6] and out[7] the row groups of their fused units (1: none; see
- * MD_FLAG_NO_ROW_GROUPS).  Host-only, no device work. */
+ * MD_FLAG_NO_ROW_GROUPS).  With neither MD_FLAG_FUSED nor MD_FLAG_NO_FUSED a
+ * batch of short sessions takes the session kernel instead of the path that
+ * out[4] or out[5] names (timed as MD_K_ATTEND; it appends in the same
+ * launch, so MD_K_APPEND then times only steps without an observation).
+ * Host-only, no device work. */
 md_status md_kernel_config(md_handle h, int32_t* out);
 
 /*

@@ -42,6 +42,8 @@ struct md_handle_s {
     bool fused_steady;   // later observes run the fused kernel
     int rg_first;        // row groups of the fused units on the first observe
     int rg_steady;       // and on later ones (1: every unit walks every row)
+    int rows_first;      // row ranges of the session kernel on the first observe
+    int rows_steady;     // and on later ones (0: the paths above)
     int64_t observed;    // observes enqueued
     Phase phase;
     const int32_t* sel_serial;   // md_select_evict's lists since the last observe
@@ -371,7 +373,9 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     // rg, fill a quarter of the grid.
     bool fused_first = dm.fused, fused_steady = dm.fused;
     int rg_first = 1, rg_steady = 1;
-    if (dm.fused) {
+    int rows_first = 0, rows_steady = 0;   // row ranges of the session kernel (0: not used)
+    const bool automatic = !(cfg->flags & (MD_FLAG_FUSED | MD_FLAG_NO_FUSED));
+    if (dm.fused || automatic) {
         int32_t hn[md::kMaxSessions], hbud[md::kMaxSessions];
         if (hipMemcpyAsync(hn, cv->n_tokens, dm.S * sizeof(int32_t), hipMemcpyDeviceToHost, hs) != hipSuccess ||
             hipMemcpyAsync(hbud, cv->budget, dm.S * sizeof(int32_t), hipMemcpyDeviceToHost, hs) !=
@@ -379,11 +383,50 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
             hipStreamSynchronize(hs) != hipSuccess)
             return MD_E_HIP;
         int64_t first = 0, steady = 0;
+        int64_t tok_first = 0, tok_steady = 0, max_first = 0, max_steady = 0;   // tokens, all and of one session
         for (int s = 0; s < dm.S; ++s) {
             const int64_t n = hn[s] > 0 ? hn[s] : 0;
             const int64_t b = hbud[s] >= 0 ? (int64_t)hbud[s] + 1 : n;
+            const int64_t k = std::min(n, b);
             first += (n + dm.T - 1) / dm.T;
-            steady += (std::min(n, b) + dm.T - 1) / dm.T;
+            steady += (k + dm.T - 1) / dm.T;
+            tok_first += n;
+            tok_steady += k;
+            max_first = std::max(max_first, n);
+            max_steady = std::max(max_steady, k);
+        }
+        // Session kernel: short sessions whose rows all fit its LDS (whatever
+        // they grow to, so by the page table's capacity).  Each session takes
+        // as many row ranges as give every CU a workgroup, of equal numbers of
+        // rows.  It is picked when no workgroup has much more to read than an
+        // even share over the CUs: it saves the append's launch and the rows'
+        // exchange or the logits' way through memory, about 16 us, the time
+        // of 1,560 tokens of one row on one CU (25 GB/s of the full chip's
+        // rate).  Measured per step, sessions of 1,700 tokens at 30-40 %
+        // budget: 1 (1.5B shape) 28 against 37 us on the multi-kernel path, 4
+        // 32 against 46, 16 53 against 68 on the fused kernel, 32 80 against
+        // 85; 24 of 1,000-1,700 tokens at 50 % (uneven: the longest has 27 %
+        // more than the mean) 92 against 88, left to the fused kernel.
+        dm.rows_nc = automatic ? md::rows_chunks(dm.G * dm.W, dm.W, (int64_t)dm.MP * dm.P) : 0;
+        if (dm.rows_nc > 0) {
+            const int most = std::max(1, std::min(n_cu / dm.S, md::kMaxRowRanges));
+            const int rows = (dm.LHkv + most - 1) / most;   // rows per workgroup
+            const int rg = (dm.LHkv + rows - 1) / rows;
+            const int64_t rounds = ((int64_t)dm.S * rg + n_cu - 1) / n_cu;
+            auto pays = [&](int64_t tokens, int64_t longest) {
+                return longest * rows * rounds < tokens * dm.LHkv / n_cu + 1560;
+            };
+            rows_first = pays(tok_first, max_first) ? rg : 0;
+            rows_steady = pays(tok_steady, max_steady) ? rg : 0;
+            dm.rows_rg = std::max(rows_first, rows_steady);
+            if (dm.rows_rg > 0 &&
+                hipFuncSetAttribute(md::rows_kernel(dm.G * dm.W, dm.quant, dm.W),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)md::rows_lds_bytes(dm.G * dm.W, dm.rows_nc, dm.W)) != hipSuccess) {
+                (void)hipGetLastError();
+                dm.rows_rg = 0;
+            }
+            if (dm.rows_rg == 0) dm.rows_nc = rows_first = rows_steady = 0;
         }
         const int64_t cap_units = ((int64_t)dm.MP * dm.P + dm.T - 1) / dm.T;
         const int64_t rg_allow = rows_ok && dm.LHkv >= 2 * md::kMinGroupRows
@@ -391,7 +434,7 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
                                                               dm.n_wg / std::max<int64_t>(cap_units, 1)})
                                          : 1;
         auto pick = [&](int64_t u) -> int {
-            if (u <= 0 || 2 * u >= dm.n_wg) return 1;
+            if (!dm.fused || u <= 0 || 2 * u >= dm.n_wg) return 1;
             return (int)std::max<int64_t>(1, std::min<int64_t>(rg_allow, dm.n_wg / u));
         };
         rg_first = pick(first);
@@ -403,26 +446,32 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         // units, 46.8 against 44.7 us).
         auto fills = [&](int64_t u, int rg) { return (rg > 1 ? 4 : 2) * u * rg >= dm.n_wg; };
         if (!(cfg->flags & MD_FLAG_FUSED)) {
-            fused_first = fills(first, rg_first);
-            fused_steady = fills(steady, rg_steady);
+            fused_first = dm.fused && fills(first, rg_first);
+            fused_steady = dm.fused && fills(steady, rg_steady);
         }
         if (!fused_first) rg_first = 1;
         if (!fused_steady) rg_steady = 1;
     }
     dm.rg_max = std::max(rg_first, rg_steady);
     if (dm.fused) dm.U_cap *= dm.rg_max;
-    dm.multi = dm.spill || !fused_first || !fused_steady;
+    auto runs_multi = [&] {
+        return dm.spill || (!fused_first && rows_first == 0) || (!fused_steady && rows_steady == 0);
+    };
+    dm.multi = runs_multi();
 
     // Units of a last pass that fills little of the grid split too (at most
     // the grid's worth more of them), unless the static scratch, large enough
-    // for the plain plan, cannot hold their statistics and partial masses.
+    // for the plain plan, cannot hold their statistics and partial masses
+    // (nor the session kernel's, which then gives way too).
     const int plain_units = dm.U_cap;
     dm.tail = rows_ok && dm.fused ? std::min(md::kMaxRowGroups, dm.LHkv / md::kMinTailRows) : 1;
     if (dm.tail > 1) dm.U_cap += dm.n_wg; else dm.tail = 1;
     size_t bytes = md::scratch_bytes(dm);
-    if (use_static && dm.tail > 1 && bytes > md::kStaticScratchBytes) {
+    if (use_static && bytes > md::kStaticScratchBytes) {
         dm.tail = 1;
         dm.U_cap = plain_units;
+        dm.rows_nc = dm.rows_rg = rows_first = rows_steady = 0;
+        dm.multi = runs_multi();
         bytes = md::scratch_bytes(dm);
     }
     if (use_static && bytes > md::kStaticScratchBytes) return MD_E_TOO_LARGE;
@@ -496,6 +545,8 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     h->fused_steady = fused_steady;
     h->rg_first = rg_first;
     h->rg_steady = rg_steady;
+    h->rows_first = rows_first;
+    h->rows_steady = rows_steady;
     h->observed = 0;
     h->word_tag = 0;
     h->phase = kNone;
@@ -533,6 +584,20 @@ md_status md_observe_step(md_handle h, int32_t step, const float* q, const uint1
         h->have_step = true;
         h->last_step = step;
         h->phase = kNone;
+        h->sel_serial = h->sel_count = nullptr;
+        return MD_OK;
+    }
+    const int rows = h->observed == 0 ? h->rows_first : h->rows_steady;
+    if (rows > 0) {
+        // short sessions: the append and the observation in one launch
+        hipError_t e = timed_launch_ev(h, MD_K_ATTEND, true, [&](hipEvent_t t0, hipEvent_t t1) {
+            return md::launch_rows(h->dm, h->v, h->sc, q, new_k, new_region, abar_out, rows, h->stream, t0, t1); });
+        if (e == hipSuccess && h->dm.H > 0) e = md::launch_recall(h->dm, h->v, h->sc, q, abar_out, h->stream);
+        if (e != hipSuccess) return MD_E_HIP;
+        h->observed += 1;
+        h->have_step = true;
+        h->last_step = step;
+        h->phase = kObserved;
         h->sel_serial = h->sel_count = nullptr;
         return MD_OK;
     }

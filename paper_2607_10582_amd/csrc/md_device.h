@@ -136,6 +136,22 @@ __device__ __forceinline__ bool counters_ok(int np, int nt, const Dims& dm) {
     return nt > (np - 1) * dm.P && nt <= np * dm.P;
 }
 
+// Whether the append of session s2 opens a page (takes one from the free
+// list), judged on the counters as they stand before the append: the last
+// page is full, or with region-aligned pages the token's region differs
+// from the last token's; and the page table has room.
+__device__ inline bool opens_page(const Dims& dm, const View& v, int s2, const uint8_t* __restrict__ new_region) {
+    const int np = v.n_pages[s2];
+    const int nt = v.n_tokens[s2];
+    if (!counters_ok(np, nt, dm) || np >= dm.MP) return false;
+    if (!(np > 0 && nt < np * dm.P)) return true;
+    if (!dm.aligned) return false;
+    const int p = v.page_table[(size_t)s2 * dm.MP + np - 1];
+    if (p < 0 || p >= dm.NP) return false;
+    const int slot = nt - (np - 1) * dm.P;
+    return v.region[(size_t)p * dm.P + slot - 1] != new_region[s2];
+}
+
 // Split a float32 into three bfloat16 terms with x == hi + mid + lo exactly:
 // hi and mid truncate (the differences are exact by Sterbenz's lemma), and
 // what is left has at most 8 significant bits, so lo holds it exactly.

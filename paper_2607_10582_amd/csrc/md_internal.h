@@ -37,6 +37,13 @@ constexpr int kMinGroupRows = 8;
 constexpr int kMinTailRows = 4;
 constexpr int kRowBufs = kConsumeLag + 1;       // rows of logits held in LDS
 
+// Session kernel (k_rows): eight waves per workgroup, each holding up to
+// eight chunks of 64 tokens of one row in LDS (one workgroup per CU).
+constexpr int kRowsWaves = 8;
+constexpr size_t kRowsLds = 160 * 1024 - 1024;   // dynamic LDS; the rest is its static variables
+constexpr int kMaxRowRanges = 80;   // row ranges per session at most (the last workgroup adds their masses)
+constexpr int64_t rows_capacity(int nc) { return (int64_t)nc * 64 * kRowsWaves; }   // token slots per session
+
 constexpr int kFoldChunks = 16;    // multi-kernel path: sessions of at most 2,048 tokens fold their row statistics into the mass kernel
 constexpr int kMaxOffload = 64;     // host-tier pages per session at most (one 64-bit slot mask)
 
@@ -64,6 +71,8 @@ struct Dims {
     int U_cap;     // capacity of the per-step fused unit list
     int rg_max;    // most row groups of a step that splits every unit (1: none)
     int tail;      // most row groups of the units of a step's last pass (1: never split)
+    int rows_nc;   // session kernel: 64-token chunks per wave (0: the kernel is not used)
+    int rows_rg;   // session kernel: most row ranges per session at any step
     uint32_t pin_mask;
     float rho, alpha, tau_scale;
 };
@@ -136,6 +145,9 @@ struct Scratch {
                                    // offloaded, recalled, dropped from host memory, observed there
     int32_t* recall;       // [S][H] offload tier: the listed page is recalled at this step
     int32_t* rcount;       // [S] pages each session recalls at this step
+    int32_t* rows_done;    // [S] session kernel: row ranges done (low half), void ranges (high half)
+    int32_t* rows_read;    // [1] session kernel: workgroups that have read the step's counters
+    float* rows_part;      // [S][ranges][rows_capacity] session kernel: partial masses
 };
 
 size_t scratch_bytes(const Dims& dm);
@@ -177,6 +189,16 @@ const void* attend_kernel(int G, int aligned, int quant, int window);
 // waits (bounded, ~20 ms) until all workgroups have arrived; probe[1]
 // receives the fewest arrivals any workgroup saw (probe: 2 device ints).
 hipError_t launch_attend_check(const Dims& dm, int32_t* probe, int n_wg, hipStream_t st);
+// Session kernel: the whole step's append and observation in rg row ranges
+// per session.  t0, t1: an event pair recorded by the dispatch itself.
+hipError_t launch_rows(const Dims& dm, const View& v, const Scratch& sc, const float* q, const uint16_t* new_k,
+                       const uint8_t* new_region, float* abar_out, int rg, hipStream_t st, hipEvent_t t0 = nullptr,
+                       hipEvent_t t1 = nullptr);
+size_t rows_lds_bytes(int G, int nc, int window);
+const void* rows_kernel(int G, int quant, int window);
+// 64-token chunks per wave for sessions of up to `tokens` slots and G MFMA
+// columns; 0 when the kernel cannot hold a row of them
+int rows_chunks(int G, int window, int64_t tokens);
 // fold: the mass kernel works out the row statistics itself (no
 // launch_rowstats before it; sessions of at most kFoldChunks chunks).  It
 // also writes the page scores of the sessions it observes.

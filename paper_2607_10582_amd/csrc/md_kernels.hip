@@ -54,22 +54,6 @@ hipError_t static_scratch(void** ptr) {
 
 // ---------------------------------------------------------------- append
 
-// Whether the append of session s2 opens a page (takes one from the free
-// list), judged on the counters as they stand before the append: the last
-// page is full, or with region-aligned pages the token's region differs
-// from the last token's; and the page table has room.
-__device__ bool opens_page(const Dims& dm, const View& v, int s2, const uint8_t* __restrict__ new_region) {
-    const int np = v.n_pages[s2];
-    const int nt = v.n_tokens[s2];
-    if (!counters_ok(np, nt, dm) || np >= dm.MP) return false;
-    if (!(np > 0 && nt < np * dm.P)) return true;
-    if (!dm.aligned) return false;
-    const int p = v.page_table[(size_t)s2 * dm.MP + np - 1];
-    if (p < 0 || p >= dm.NP) return false;
-    const int slot = nt - (np - 1) * dm.P;
-    return v.region[(size_t)p * dm.P + slot - 1] != new_region[s2];
-}
-
 // One block per session: the append.  The last block (highest index) also
 // lays out the step's work lists.
 // Pages leave the free list in session order: session s takes the entry
@@ -1844,6 +1828,10 @@ size_t scratch_bytes(const Dims& dm) {
     n += 3 * align256((size_t)dm.S * sizeof(unsigned long long));
     n += align256((size_t)dm.S * dm.H * sizeof(int32_t));
     n += align256((size_t)(dm.S + 1) * sizeof(int32_t));
+    if (dm.rows_nc > 0) {
+        n += align256((size_t)(dm.S + 1) * sizeof(int32_t));
+        n += align256((size_t)dm.S * dm.rows_rg * rows_capacity(dm.rows_nc) * sizeof(float));
+    }
     return n;
 }
 
@@ -1890,6 +1878,12 @@ void scratch_carve(const Dims& dm, void* base, Scratch* sc) {
     sc->ev_done = reinterpret_cast<unsigned long long*>(take((size_t)dm.S * sizeof(unsigned long long)));
     sc->recall = reinterpret_cast<int32_t*>(take((size_t)dm.S * dm.H * sizeof(int32_t)));
     sc->rcount = reinterpret_cast<int32_t*>(take((size_t)(dm.S + 1) * sizeof(int32_t)));
+    if (dm.rows_nc > 0) {
+        sc->rows_done = reinterpret_cast<int32_t*>(take((size_t)(dm.S + 1) * sizeof(int32_t)));
+        sc->rows_read = sc->rows_done + dm.S;
+        sc->rows_part = reinterpret_cast<float*>(
+            take((size_t)dm.S * dm.rows_rg * rows_capacity(dm.rows_nc) * sizeof(float)));
+    }
 }
 
 }  // namespace md

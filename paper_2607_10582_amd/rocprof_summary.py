@@ -30,7 +30,7 @@ from collections import defaultdict
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
-KERNEL_SOURCES = {"k_attend": "md_attend.hip", "k_logits": "md_kernels.hip"}
+KERNEL_SOURCES = {"k_attend": "md_attend.hip", "k_rows": "md_rows.hip", "k_logits": "md_kernels.hip"}
 HEADERS = ("md_internal.h", "md_device.h")   # included by both sources
 
 
