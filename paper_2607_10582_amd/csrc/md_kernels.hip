@@ -1155,9 +1155,9 @@ __device__ __forceinline__ void select_session(const Dims& dm, const View& v, co
                                                uint32_t tag) {
     const int s = blockIdx.x;
     __shared__ int lds[2 * 17];
-    __shared__ uint32_t s_min[16];
     __shared__ int hist[256];
-    __shared__ int sh_digit, sh_before, sh_fc, sh_prior, sh_bad;
+    __shared__ int sh_digit, sh_before, sh_prior, sh_bad;
+    __shared__ unsigned long long s_min[16];
     const int tid = threadIdx.x;
     const uint32_t kInf = 0x7F800000u;
     const float* ps = sc.pscore + (size_t)s * dm.MP;
@@ -1166,7 +1166,7 @@ __device__ __forceinline__ void select_session(const Dims& dm, const View& v, co
     // The runs split the page-table capacity, not the session's pages, so
     // the scores, serials and table entries go out with the counters rather
     // than after them; entries past the session's pages are read but not used.
-    const int per = (dm.MP + kSelThreads - 1) / kSelThreads;
+    const int per = (dm.MP + (int)blockDim.x - 1) / (int)blockDim.x;
     const int i0 = min(dm.MP, tid * per), ie = min(dm.MP, i0 + per);
     float sv[kPerThread];
     int pv[kPerThread], sr[kPerThread];
@@ -1180,125 +1180,173 @@ __device__ __forceinline__ void select_session(const Dims& dm, const View& v, co
             if (Apply || dm.aligned) pv[k] = ptab[i0 + k];
         }
     }
-    if (Apply && tid == 0) sh_fc = v.free_count[0];
+    const int fc = Apply ? v.free_count[0] : 0;   // changes only in the last block, once every block has it
     const int np = v.n_pages[s], nt = v.n_tokens[s], B = v.budget[s];
     const int need = v.n_live[s] - B;
     const bool active = sc.valid[s] && need > 0 && np > 0;
-    if (!Apply && !active) {
+    const int last = (int)gridDim.x - 1;
+    if (!active && (!Apply || s != last)) {
+        // nothing to select (most sessions at most steps: a page covers P
+        // steps' tokens), and no wait for anyone
         if (tid == 0) {
             ev_count[s] = 0;
             infeasible[s] = 0;
+            if (Apply) {
+                const unsigned long long t = (unsigned long long)(tag & kWordTagMask) << 32;
+                const bool bad = fc < 0;
+                __hip_atomic_store(sc.ev_word + s, t | (unsigned long long)(bad ? 1u << 31 : 0u), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(sc.ev_done + s, t | (bad ? 0ull : 1ull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (bad) atomicOr(sc.status, kDevCorrupt);
+                sc.freed[s] = 0;
+            }
         }
         return;
     }
+    bool ev[kPerThread];
+#pragma unroll
+    for (int k = 0; k < kPerThread; ++k) ev[k] = false;
     const int i1 = active ? min(np, ie) : i0;
-    uint32_t key[kPerThread];
-    int wt[kPerThread];
-    int wsum = 0;
-    uint32_t kmin = kInf;
+    int n_ev = 0, live_ev = 0, before = 0;   // pages and tokens that go; pages before this thread's run
+    bool infeas = false;
+    if (active) {
+        uint32_t key[kPerThread];
+        int wt[kPerThread];
+        int wsum = 0;
+        uint32_t kmin = kInf;
 #pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-        const int i = i0 + k;
-        key[k] = kInf;
-        wt[k] = 0;
-        if (i < i1) {
-            key[k] = __float_as_uint(sv[k]);
-            wt[k] = page_tokens(dm, v, pv[k], i, np, nt);
-            if (key[k] < kInf) wsum += wt[k];
-            kmin = min(kmin, key[k]);
+        for (int k = 0; k < kPerThread; ++k) {
+            const int i = i0 + k;
+            key[k] = kInf;
+            wt[k] = 0;
+            if (i < i1) {
+                key[k] = __float_as_uint(sv[k]);
+                wt[k] = page_tokens(dm, v, pv[k], i, np, nt);
+                if (key[k] < kInf) wsum += wt[k];
+                kmin = min(kmin, key[k]);
+            }
         }
-    }
-    kmin = wave_min_u32(kmin);
-    if (lane_id() == 0) s_min[tid >> 6] = kmin;
-    int total;
-    block_exclusive_scan(wsum, lds, &total);   // its barriers publish s_min too
-    const bool infeas = active && total < need;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) kmin = min(kmin, s_min[w]);
-    // the smallest key's weight, and each thread's share of it before its run
-    int teq = 0;
+        // the smallest key and the first page that holds it (index, weight)
+        const uint32_t wmin = wave_min_u32(kmin);
+        uint32_t first = ~0u;
 #pragma unroll
-    for (int k = 0; k < kPerThread; ++k)
-        if (key[k] == kmin && key[k] < kInf) teq += wt[k];
-    int at_min;
-    int run = block_exclusive_scan(teq, lds, &at_min);
-    uint32_t T = kmin;
-    int rem = need;
-    if (active && !infeas && at_min < need) {
-        uint32_t prefix = 0, pmask = 0;
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            if (tid < 256) hist[tid] = 0;
-            __syncthreads();
+        for (int k = kPerThread - 1; k >= 0; --k)
+            if (key[k] == wmin && key[k] < kInf) first = (uint32_t)(i0 + k) << 8 | (uint32_t)wt[k];
+        first = wave_min_u32(first);
+        if (lane_id() == 0) s_min[tid >> 6] = (unsigned long long)wmin << 32 | first;
+        // every table entry is in its register before any thread moves one
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        lds_sync();
+        unsigned long long best = s_min[0];
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) best = min(best, s_min[w]);
+        kmin = (uint32_t)(best >> 32);
+        if (kmin < kInf && (int)(best & 0xffu) >= need) {
+            // that page alone covers the need (a steady decode step, one
+            // token over the budget): it is the selection, and no scan runs
+            const int i_one = (int)((best >> 8) & 0xffffffu);
+#pragma unroll
+            for (int k = 0; k < kPerThread; ++k) ev[k] = i0 + k == i_one && i_one < i1;
+            n_ev = 1;
+            live_ev = (int)(best & 0xffu);
+            before = i0 > i_one ? 1 : 0;
+        } else {
+            int total;
+            {
+                const int m[1] = {wsum};
+                int ex[1], tot[1];
+                block_exclusive_scan_n<1, true>(m, lds, ex, tot);
+                total = tot[0];
+            }
+            infeas = total < need;
+            // the smallest key's weight, and each thread's share of it
+            // before its run
+            int teq = 0;
+#pragma unroll
+            for (int k = 0; k < kPerThread; ++k)
+                if (key[k] == kmin && key[k] < kInf) teq += wt[k];
+            int at_min;
+            int run = block_exclusive_scan(teq, lds, &at_min);
+            uint32_t T = kmin;
+            int rem = need;
+            if (!infeas && at_min < need) {
+                uint32_t prefix = 0, pmask = 0;
+                for (int shift = 24; shift >= 0; shift -= 8) {
+                    if (tid < 256) hist[tid] = 0;
+                    lds_sync();
+#pragma unroll
+                    for (int k = 0; k < kPerThread; ++k) {
+                        if (key[k] < kInf && (key[k] & pmask) == prefix)
+                            atomicAdd(&hist[(key[k] >> shift) & 255u], wt[k]);
+                    }
+                    lds_sync();
+                    // inclusive scan of the 256 bins by the first four waves;
+                    // every thread of the block reaches both barriers
+                    int hv = 0, incl = 0;
+                    if (tid < 256) {
+                        hv = hist[tid];
+                        incl = wave_incl_sum(hv);
+                        if (lane_id() == 63) lds[tid >> 6] = incl;
+                    }
+                    lds_sync();
+                    if (tid < 256) {
+                        const int wid = tid >> 6;
+                        for (int w = 0; w < wid; ++w) incl += lds[w];
+                        const int excl = incl - hv;
+                        if (excl < rem && rem <= incl) {
+                            sh_digit = tid;
+                            sh_before = excl;
+                        }
+                    }
+                    lds_sync();
+                    prefix |= (uint32_t)sh_digit << shift;
+                    pmask |= 0xFFu << shift;
+                    rem -= sh_before;
+                    lds_sync();
+                }
+                T = prefix;
+                // weights of the key == T pages before this thread's run
+                teq = 0;
+#pragma unroll
+                for (int k = 0; k < kPerThread; ++k)
+                    if (key[k] == T) teq += wt[k];
+                int dummy;
+                run = block_exclusive_scan(teq, lds, &dummy);
+            }
+            int my_ev = 0, my_live = 0;
 #pragma unroll
             for (int k = 0; k < kPerThread; ++k) {
-                if (key[k] < kInf && (key[k] & pmask) == prefix)
-                    atomicAdd(&hist[(key[k] >> shift) & 255u], wt[k]);
-            }
-            __syncthreads();
-            // inclusive scan of the 256 bins by the first four waves; every
-            // thread of the block reaches both barriers
-            int hv = 0, incl = 0;
-            if (tid < 256) {
-                const int lane = lane_id();
-                hv = hist[tid];
-                incl = hv;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int t2 = __shfl_up(incl, o);
-                    if (lane >= o) incl += t2;
+                bool e = false;
+                if (i0 + k < i1 && key[k] < kInf) {
+                    if (infeas) {
+                        e = true;
+                    } else if (key[k] < T) {
+                        e = true;
+                    } else if (key[k] == T) {
+                        e = run < rem;
+                        run += wt[k];
+                    }
                 }
-                if (lane == 63) lds[tid >> 6] = incl;
+                ev[k] = e;
+                my_ev += e ? 1 : 0;
+                my_live += e ? wt[k] : 0;
             }
-            __syncthreads();
-            if (tid < 256) {
-                const int wid = tid >> 6;
-                for (int w = 0; w < wid; ++w) incl += lds[w];
-                const int excl = incl - hv;
-                if (excl < rem && rem <= incl) {
-                    sh_digit = tid;
-                    sh_before = excl;
-                }
-            }
-            __syncthreads();
-            prefix |= (uint32_t)sh_digit << shift;
-            pmask |= 0xFFu << shift;
-            rem -= sh_before;
-            __syncthreads();
+            const int m[2] = {my_ev, my_live};
+            int ex[2], tot[2];
+            block_exclusive_scan_n<2, true>(m, lds, ex, tot);
+            n_ev = tot[0];
+            live_ev = tot[1];
+            before = ex[0];
         }
-        T = prefix;
-        // weights of the key == T pages before this thread's run
-        teq = 0;
-#pragma unroll
-        for (int k = 0; k < kPerThread; ++k)
-            if (key[k] == T) teq += wt[k];
-        int dummy;
-        run = block_exclusive_scan(teq, lds, &dummy);
     }
-    bool ev[kPerThread];
-    int my_ev = 0, my_live = 0;
-#pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-        bool e = false;
-        if (i0 + k < i1 && key[k] < kInf) {
-            if (infeas) {
-                e = true;
-            } else if (key[k] < T) {
-                e = true;
-            } else if (key[k] == T) {
-                e = run < rem;
-                run += wt[k];
-            }
-        }
-        ev[k] = e;
-        my_ev += e ? 1 : 0;
-        my_live += e ? wt[k] : 0;
+    if (Apply && tid == 0) {
+        sh_prior = 0;
+        sh_bad = 0;
+        __hip_atomic_store(sc.ev_word + s,
+                           ((unsigned long long)(tag & kWordTagMask) << 32) |
+                               ((unsigned long long)(fc < 0 ? 1 : 0) << 31) | (unsigned long long)n_ev,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    int ex[2], tot[2];
-    {
-        const int m[2] = {my_ev, my_live};
-        block_exclusive_scan_n<2>(m, lds, ex, tot);
-    }
-    const int n_ev = tot[0];
-    int pos = ex[0];
+    int pos = before;
     int32_t* out = ev_serial + (size_t)s * dm.MP;
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k)
@@ -1311,17 +1359,7 @@ __device__ __forceinline__ void select_session(const Dims& dm, const View& v, co
     if (!Apply) return;
 
     // ---- the compaction of this session, and the free list
-    const int fc = sh_fc;   // read by thread 0 before the barriers of the scans
-    const int last = (int)gridDim.x - 1;
-    if (tid == 0) {
-        sh_prior = 0;
-        sh_bad = 0;
-        __hip_atomic_store(sc.ev_word + s,
-                           ((unsigned long long)(tag & kWordTagMask) << 32) |
-                               ((unsigned long long)(fc < 0 ? 1 : 0) << 31) | (unsigned long long)n_ev,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
+    lds_sync();
     // look-back: the counts of the sessions before this one (all of them for
     // the last block)
     int prior = 0, bad = 0;
@@ -1344,7 +1382,7 @@ __device__ __forceinline__ void select_session(const Dims& dm, const View& v, co
     }
     if (lane_id() == 0 && prior > 0) atomicAdd(&sh_prior, prior);
     if (lane_id() == 0 && bad) sh_bad = 1;
-    __syncthreads();
+    lds_sync();
     const int base = fc + sh_prior;
     const bool ok = !sh_bad && fc >= 0 && base + n_ev <= dm.NP;
     // Whether this block applies its selection, told to the last block
@@ -1359,15 +1397,16 @@ __device__ __forceinline__ void select_session(const Dims& dm, const View& v, co
     }
     if (ok && n_ev > 0) {
         // kept pages move down in order; the evicted ones' ids go onto the
-        // free list at the session's places.  Every table entry was read
-        // before the scans' barriers.
-        int kpos = min(i0, np) - ex[0], gpos = ex[0];
+        // free list at the session's places
+        int kpos = min(i0, np) - before, gpos = before;
 #pragma unroll
         for (int k = 0; k < kPerThread; ++k) {
             if (i0 + k < i1) {
                 if (!ev[k]) {
-                    ptab[kpos] = pv[k];
-                    ser[kpos] = sr[k];
+                    if (kpos != i0 + k) {   // pages before the first evicted one stay
+                        ptab[kpos] = pv[k];
+                        ser[kpos] = sr[k];
+                    }
                     ++kpos;
                 } else {
                     if (ok && base + gpos >= 0 && base + gpos < dm.NP) v.free_list[base + gpos] = pv[k];
@@ -1386,9 +1425,9 @@ __device__ __forceinline__ void select_session(const Dims& dm, const View& v, co
             const int kept = np - n_ev;
             v.n_pages[s] = kept;
             v.n_tokens[s] = last_kept ? nt - n_ev * dm.P : kept * dm.P;
-            if (dm.aligned) v.n_live[s] -= tot[1];
+            if (dm.aligned) v.n_live[s] -= live_ev;
             atomicAdd(&sc.counters[2], (unsigned long long)n_ev);
-            atomicAdd(&sc.counters[3], (unsigned long long)tot[1]);
+            atomicAdd(&sc.counters[3], (unsigned long long)live_ev);
         }
     }
     if (s != last) return;
@@ -1423,16 +1462,20 @@ __global__ void __launch_bounds__(kSelThreads) k_evict(Dims dm, View v, Scratch 
     select_session<true>(dm, v, sc, ev_serial, ev_count, infeasible, tag);
 }
 
+// Threads of a selection block: 256 where each still takes at most
+// kPerThread pages (fewer waves to start and to meet).
+static int select_threads(const Dims& dm) { return dm.MP <= 256 * kPerThread ? 256 : kSelThreads; }
+
 hipError_t launch_select(const Dims& dm, const View& v, const Scratch& sc, int32_t* ev_serial,
                          int32_t* ev_count, uint8_t* infeasible, hipStream_t st) {
-    hipLaunchKernelGGL(k_select, dim3(dm.S), dim3(kSelThreads), 0, st, dm, v, sc, ev_serial,
+    hipLaunchKernelGGL(k_select, dim3(dm.S), dim3(select_threads(dm)), 0, st, dm, v, sc, ev_serial,
                        ev_count, infeasible);
     return hipGetLastError();
 }
 
 hipError_t launch_evict(const Dims& dm, const View& v, const Scratch& sc, int32_t* ev_serial,
                         int32_t* ev_count, uint8_t* infeasible, uint32_t tag, hipStream_t st) {
-    hipLaunchKernelGGL(k_evict, dim3(dm.S), dim3(kSelThreads), 0, st, dm, v, sc, ev_serial,
+    hipLaunchKernelGGL(k_evict, dim3(dm.S), dim3(select_threads(dm)), 0, st, dm, v, sc, ev_serial,
                        ev_count, infeasible, tag);
     return hipGetLastError();
 }
