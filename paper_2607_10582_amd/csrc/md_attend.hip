@@ -89,12 +89,35 @@ struct AttendArgs {
     const int32_t* rgs;           // [S] row groups of each session's units (1: every row)
 };
 
+// The kernel's arguments read again from the argument segment where they are
+// used.  What the pass bookkeeping and the end of a unit read would otherwise
+// be held in scalar registers through the row loop, which has none to spare:
+// the row loop then fetches its own values back from spill lanes.
+#define MD_ARG_SPACE __attribute__((address_space(4)))
+__device__ __forceinline__ const MD_ARG_SPACE char* arg_segment() {
+    auto* p = (const MD_ARG_SPACE char*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ const MD_ARG_SPACE AttendDims* cold_dims() {
+    return (const MD_ARG_SPACE AttendDims*)arg_segment();
+}
+__device__ __forceinline__ const MD_ARG_SPACE AttendArgs* cold_args() {
+    constexpr size_t at = (sizeof(AttendDims) + alignof(AttendArgs) - 1) / alignof(AttendArgs) * alignof(AttendArgs);
+    return (const MD_ARG_SPACE AttendArgs*)(arg_segment() + at);
+}
+// A global pointer read from there (a plain one would be a flat access).
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* global(T* p) {
+    return (__attribute__((address_space(1))) T*)p;
+}
+
 // LDS row stride (floats) of a head's values: W waves of KT tiles
 __host__ __device__ constexpr int tstride(int W, int KT) { return 16 * W * KT + 4; }
 
 struct Lds {
     float* rowbuf;    // [kRowBufs][G][tstride] 2^(logit - wave max) of the held rows
-    uint32_t* qs;     // [2][3][G][64] hi, mid, lo bf16 query terms (pairs) of two rows
+    uint32_t* qs;     // [2][3 G + 1][64] hi, mid, lo bf16 query terms (pairs) of two rows, a block of zeros
     float2* wstat;    // [2][W][16] per-wave row statistics
     float2* norm;     // [2][16] row normalisers (M, 1 / Lambda)
     int* vflag;       // [1] the unit's step is void: a non-finite query, or a wait ran out
@@ -106,7 +129,12 @@ struct Lds {
 __host__ __device__ inline size_t rowbuf_bytes(int G, int W, int KT) {
     return (size_t)kRowBufs * G * tstride(W, KT) * sizeof(float);
 }
-__host__ __device__ inline size_t qs_bytes(int G) { return (size_t)2 * 3 * G * 64 * sizeof(uint32_t); }
+__host__ __device__ constexpr int qs_words(int G) { return (3 * G + 1) * 64; }   // of one row
+__host__ __device__ inline size_t qs_bytes(int G) { return (size_t)2 * qs_words(G) * sizeof(uint32_t); }
+// Word of the pair of dims (d, d + 1) of head hd's terms: the 16-byte pieces
+// of four neighbouring heads are rotated against each other, since unrotated
+// every head's piece of the same dims falls on the same banks.
+__host__ __device__ constexpr int q_word(int hd, int d2) { return d2 ^ ((hd & 3) << 4); }
 __host__ __device__ inline size_t wstat_bytes(int W) { return (size_t)2 * W * 16 * sizeof(float2); }
 constexpr size_t kNormBytes = (size_t)2 * 16 * sizeof(float2);
 constexpr size_t kFlagBytes = 16;
@@ -178,6 +206,26 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
 }
 #undef MD_DPP
 
+// Max / sum over the four 16-lane rows of a wave, in every lane.  The
+// permlane swaps run on the VALU: a shuffle through LDS costs a round trip
+// of its own, and a row needs four one after the other.
+__device__ __forceinline__ float rows_max(float v) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ __forceinline__ float rows_sum(float v) {
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+// The value of lane i + 8 (mod 16) of the same 16-lane row.
+__device__ __forceinline__ float half_row(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true));   // row_ror:8
+}
+
 struct Unit {
     int s, j, ntok, nt_s, nu, us;
     uint64_t deadline;   // real-time tick after which the unit stops waiting
@@ -188,7 +236,7 @@ struct Unit {
     int r0, r1, grp, rg, ubase;
 };
 
-__device__ void claim_sessions(const AttendArgs& a, int* xs, int lane_no, int cap);
+__device__ void claim_sessions(int* xs, int lane_no, int cap);
 
 // First query row (layer * Hq + KV head * G) of (layer, KV head) row r:
 // with Hq = Hkv * G that is r * G.
@@ -213,9 +261,19 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
                                             int cap, unsigned long long* next_box) {
     constexpr int KQ = (W * NH * 32 + 64 * W - 1) / (64 * W);   // float4 of the query row per lane
     const int G = dm.G;
-    const int h = lane & 15;          // MFMA column: query head of the group
+    const int h = lane & 15;          // MFMA column
     const int g = lane >> 4;          // k-group of A/B, row quad of C
-    const int hh = min(h, G - 1);     // in-bounds head for the unused columns
+    // Groups of up to eight heads (PK) put the hi and mid terms of a query
+    // side by side into columns 0 .. 7 and 8 .. 15 of one MFMA and the lo
+    // terms (columns 0 .. 7) into a second: two instructions per 32 dims
+    // rather than three.  The halves' sums are then added crosswise, and each
+    // half goes on with two of the four tiles, so the row's softmax takes
+    // eight values per lane rather than sixteen.
+    constexpr bool PK = W * NH <= 8 && KT == 4;
+    constexpr int NT = PK ? KT / 2 : KT;   // tiles per lane after the MFMA
+    const int hc = PK ? h & 7 : h;         // the lane's query head of the group
+    const int ub = PK ? (h >> 3) * NT : 0; // its first tile
+    const int hh = min(hc, G - 1);         // in-bounds head for the unused columns
     const uint32_t voff = 16u * lane;   // piece (8-dim block 4j + g, token h) of a 16-token block
     constexpr int kT = 16 * W * KT;   // tokens per unit
     constexpr int kTs = tstride(W, KT);
@@ -258,23 +316,30 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
 #pragma unroll
         for (int u = 0; u < KT; ++u) lims |= (uint32_t)__builtin_amdgcn_readlane(mylim, u) << (8 * u);
     }
-    // Window: bit 4u + i marks this lane's logit column (window query
-    // h / Gq) of tile u, token 4g + i, as inserted after that query's step.
-    uint32_t unseen = 0;
-    if constexpr (WN) {
-        const int t_lim = a.clock[un.s] - (dm.Wn - 1 - min(h / dm.Gq, dm.Wn - 1));
+    // Bit 4u + i of `gone`: this lane's value of its tile u (of NT), token
+    // 4g + i, is no logit: past the unit's end, without a page, a hole, or
+    // (window) inserted after the step of the column's query h / Gq.  One
+    // register: as conditions the masks of every value would be hoisted
+    // out of the row loop into scalar registers, and from there spilled.
+    uint32_t gone = 0;
+    {
+        int t_lim = 0;
+        if constexpr (WN) t_lim = a.clock[un.s] - (dm.Wn - 1 - min(hc / dm.Gq, dm.Wn - 1));
 #pragma unroll
-        for (int u = 0; u < KT; ++u) {
-            const int slot = __builtin_amdgcn_readlane(myslot, u);
-            if ((vmask >> u) & 1ull) {
+        for (int u = 0; u < NT; ++u) {
+            const int t = ub + u;
+            const bool ok = (vmask >> t) & 1ull;
+            const int slot = WN ? __shfl(myslot, t) : 0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    unseen |= (a.t_ins[slot + 4 * g + i] > t_lim) ? 1u << (4 * u + i) : 0u;
+            for (int i = 0; i < 4; ++i) {
+                bool no = !ok || wtok0 + 16 * t + 4 * g + i >= un.ntok;
+                if constexpr (AL) no |= 4 * g + i >= (int)((lims >> (8 * t)) & 0xffu);
+                if constexpr (WN) no |= ok && a.t_ins[slot + 4 * g + i] > t_lim;
+                gone |= no ? 1u << (4 * u + i) : 0u;
             }
         }
     }
-    const bool wave_full = (vmask & kAll) == kAll && wtok0 + 16 * KT <= un.ntok && (!AL || lims == 0x10101010u) &&
-                           (!WN || !__any(unseen != 0));
+    const bool wave_full = !__any(gone != 0);
     // Quantised tier: bit u of qmask marks tile u as 8-bit codes (its page's
     // format); wave-uniform.
     uint32_t qmask = 0;
@@ -283,16 +348,28 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         qmask = (uint32_t)(__ballot(qz) & kAll);
     }
 
-    // K tile u of row r in the MFMA A layout: the pool keeps each block of
+    // K tile u of a row in the MFMA A layout: the pool keeps each block of
     // 16 tokens as [d / 8][16][8], so load j reads 1 KiB contiguous and lane
     // (h, g) gets token h's dims 32j + 8g .. +7.  A tile without cached
     // tokens, or past the last row, reads the pool's first tile (its logits
-    // are masked), so loads never branch.
-    auto load_tile = [&](u32x4 (&rg)[4], int r, int u) {
-        const bool ok = r < r_end && ((vmask >> u) & 1ull);
-        const int slot = __builtin_amdgcn_readlane(myslot, u);
-        const size_t e = ok ? ((size_t)(slot >> dm.Pshift) * dm.LHkv + r) * dm.P + (slot & (dm.P - 1)) : 0;
-        gbytes base = uni_ptr(a.k_pool + e * kHeadDim);
+    // are masked), so loads never branch.  Lane u < KT keeps tile u's address
+    // in the row to load next and moves it on once per row (next_row): two
+    // register reads per tile in place of its address from the row number.
+    const uint64_t pool = reinterpret_cast<uint64_t>(a.k_pool);
+    uint64_t kaddr = pool;
+    uint32_t kstep = 0;
+    if (myok) {
+        kaddr = pool + (((size_t)(myslot >> dm.Pshift) * dm.LHkv + r_beg) * dm.P + (myslot & (dm.P - 1))) *
+                           (kHeadDim * sizeof(uint16_t));
+        kstep = (uint32_t)dm.P * (kHeadDim * sizeof(uint16_t));
+    }
+    auto next_row = [&](int r) {   // the tiles of row r are loaded next
+        kaddr = r < r_end ? kaddr + kstep : pool;
+    };
+    auto load_tile = [&](u32x4 (&rg)[4], int u) {
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)kaddr, u);
+        const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(kaddr >> 32), u);
+        gbytes base = (gbytes)(((uint64_t)hi << 32) | lo);
         if constexpr (QT) {
             // a quantised block: codes in its first 2 KiB (rg[0], rg[1]), the
             // scale at byte 2048 (rg[2]); rg[3] takes the next 16 bytes of
@@ -335,7 +412,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         }
     };
     auto store_q = [&](int r) {
-        uint32_t* qb = sm.qs + (size_t)(r & 1) * 3 * G * 64;
+        uint32_t* qb = sm.qs + (size_t)(r & 1) * qs_words(G);
         bool bad = false;
 #pragma unroll
         for (int k = 0; k < KQ; ++k) {
@@ -350,7 +427,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
                 }
 #pragma unroll
                 for (int p = 0; p < 3; ++p)
-                    *reinterpret_cast<uint2*>(qb + (p * G + hd) * 64 + d2) =
+                    *reinterpret_cast<uint2*>(qb + (p * G + hd) * 64 + q_word(hd, d2)) =
                         make_uint2(t[p][0] | (t[p][1] << 16), t[p][2] | (t[p][3] << 16));
             }
         }
@@ -484,12 +561,16 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // publishes all heads (lane h = head h).
     auto publish = [&](int r) {
         if (wv == (r & (W - 1)) && lane < G) {
+            float2 st[W];
             float um = -INFINITY, ul = 0.0f;
 #pragma unroll
             for (int pw = 0; pw < W; ++pw) {
-                const float2 st = sm.wstat[((r & 1) * W + pw) * 16 + lane];
-                merge_stat(um, ul, st.x, st.y);
+                st[pw] = sm.wstat[((r & 1) * W + pw) * 16 + lane];
+                um = fmaxf(um, st[pw].x);
             }
+            const float us = um == -INFINITY ? 0.0f : um;
+#pragma unroll
+            for (int pw = 0; pw < W; ++pw) ul += st[pw].y * hw_exp2(st[pw].x - us);
             unsigned long long* p = stat_word(r, un.j, lane);
             __hip_atomic_store(p, tag_hi | __float_as_uint(um), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(p + 1, tag_hi | __float_as_uint(ul), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -560,6 +641,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // iteration issues them: row 0's tiles, the requests and row 1's query,
     // row 1's tiles
     load_q(r_beg);
+    if (PK && wv < 2) sm.qs[wv * qs_words(G) + 3 * G * 64 + lane] = 0u;
     store_q(r_beg);
     lds_sync();
     // Two rings of four tiles: row r's tiles sit in ring r & 1, and the
@@ -567,11 +649,13 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // MFMA, so two rows of loads are in flight while a wave works on a row.
     u32x4 ringA[KT][4], ringB[KT][4];
 #pragma unroll
-    for (int u = 0; u < KT; ++u) load_tile(ringA[u], r_beg, u);
+    for (int u = 0; u < KT; ++u) load_tile(ringA[u], u);
+    next_row(r_beg + 1);
     if (((r_beg - 5) & (W - 1)) == wv) load_norm(r_beg);
     load_q(min(r_beg + 1, last));
 #pragma unroll
-    for (int u = 0; u < KT; ++u) load_tile(ringB[u], min(r_beg + 1, last + 2), u);
+    for (int u = 0; u < KT; ++u) load_tile(ringB[u], u);
+    next_row(r_beg + 2);
 
     // Row r:
     //   1. logits of the four tiles on MFMA, k-chunk by k-chunk (the chunk's
@@ -587,7 +671,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // every wave at issue, while spread out the issue waits overlap the
     // work of the row.
     auto do_row = [&](u32x4 (&ring)[KT][4], int row) {
-        const uint32_t* qb = sm.qs + (size_t)(row & 1) * 3 * G * 64 + hh * 64 + 4 * g;
+        const uint32_t* qrow = sm.qs + (size_t)(row & 1) * qs_words(G);
         // Quantised tiles: the scale (the same 16 bytes in every lane) goes
         // to a scalar, and the codes are widened to bf16 (exact) in place,
         // so the MFMA loop below is the plain one and holds no second copy
@@ -611,73 +695,102 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         f32x4 c[KT];
 #pragma unroll
         for (int u = 0; u < KT; ++u) c[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // (the lane is made opaque so that the pieces' addresses, rotated by
+        // head, are worked out here rather than kept in registers)
+        int lq = lane;
+        asm volatile("" : "+v"(lq));
+        const int hq = min(PK ? lq & 7 : lq & 15, G - 1), gq = (lq >> 4) * 4;
+        if constexpr (PK) {
+            const bool hi8 = lq & 8;
+            const uint32_t* q0 = qrow + ((hi8 ? G : 0) + hq) * 64;              // hi, mid
+            const uint32_t* q1 = qrow + (hi8 ? 3 * G : 2 * G + hq) * 64;        // lo, zeros
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            u32x4 bq[3];
+            for (int j = 0; j < 4; ++j) {
+                const int o = q_word(hq, 16 * j + gq);
+                const u32x4 b0 = *reinterpret_cast<const u32x4*>(q0 + o);
+                const u32x4 b1 = *reinterpret_cast<const u32x4*>(q1 + o);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) bq[p] = *reinterpret_cast<const u32x4*>(qb + p * G * 64 + 16 * j);
+                for (int u = 0; u < KT; ++u)
+                    c[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, ring[u][j]), __builtin_bit_cast(bf16x8, b0), c[u], 0, 0, 0);
 #pragma unroll
-            for (int u = 0; u < KT; ++u) {
+                for (int u = 0; u < KT; ++u)
+                    c[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, ring[u][j]), __builtin_bit_cast(bf16x8, b1), c[u], 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                u32x4 bq[3];
+                const uint32_t* qb = qrow + hq * 64 + q_word(hq, 16 * j + gq);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) bq[p] = *reinterpret_cast<const u32x4*>(qb + p * G * 64);
 #pragma unroll
                 for (int p = 0; p < 3; ++p)
-                    c[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, ring[u][j]), __builtin_bit_cast(bf16x8, bq[p]), c[u], 0, 0, 0);
+#pragma unroll
+                    for (int u = 0; u < KT; ++u)
+                        c[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, ring[u][j]), __builtin_bit_cast(bf16x8, bq[p]), c[u], 0, 0, 0);
             }
         }
-        if constexpr (QT) {
-#pragma unroll
-            for (int u = 0; u < KT; ++u)
-                if ((qmask >> u) & 1u) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) c[u][i] *= qsc[u];
-                }
-        }
-        load_tile(ring[0], row + 2, 0);
+        load_tile(ring[0], 0);
         use_loads(row);
-        load_tile(ring[1], row + 2, 1);
+        load_tile(ring[1], 1);
         if (row + 1 < r_end) store_q(row + 1);
         issue_loads(row);
         load_q(min(row + 2, last));
-        load_tile(ring[2], row + 2, 2);
+        load_tile(ring[2], 2);
 
-        // Base-2 logits of the wave's 64 tokens (lane: head h, tokens
-        // 16 u + 4 g + i), their maximum and the sum of 2^(logit - max) per
-        // head; the LDS row keeps 2^(logit - max).
-        float xs[KT][4];
+        // Base-2 logits (lane: head hc, tokens 16 (ub + u) + 4 g + i), their
+        // maximum and the sum of 2^(logit - max) per head over the wave's 64
+        // tokens; the LDS row keeps 2^(logit - max).
+        float xs[NT][4];
+        const bool up = h >= 8;
 #pragma unroll
-        for (int u = 0; u < KT; ++u)
+        for (int u = 0; u < NT; ++u) {
+            float f = kLogitScale;
+            if constexpr (QT) f *= (PK && up) ? qsc[(u + NT) % KT] : qsc[u];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) xs[u][i] = c[u][i] * kLogitScale;
-        if (!wave_full) {   // tokens past the unit's end, tiles without a page
+            for (int i = 0; i < 4; ++i) {
+                float x = c[u][i];
+                if constexpr (PK) {
+                    const float x0 = c[u][i] + half_row(c[u][i]);
+                    const float x1 = c[(u + NT) % KT][i] + half_row(c[(u + NT) % KT][i]);
+                    x = up ? x1 : x0;
+                }
+                xs[u][i] = x * f;
+            }
+        }
+        if (!wave_full) {
+            uint32_t no = gone;
+            asm volatile("" : "+v"(no));   // tested here, not hoisted
 #pragma unroll
-            for (int u = 0; u < KT; ++u)
+            for (int u = 0; u < NT; ++u)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (!((vmask >> u) & 1ull) || wtok0 + 16 * u + 4 * g + i >= un.ntok ||
-                        (AL && 4 * g + i >= (int)((lims >> (8 * u)) & 0xffu)) ||
-                        (WN && ((unseen >> (4 * u + i)) & 1u)))
-                        xs[u][i] = -INFINITY;
+                    if ((no >> (4 * u + i)) & 1u) xs[u][i] = -INFINITY;
         }
         float mx = -INFINITY;
 #pragma unroll
-        for (int u = 0; u < KT; ++u)
+        for (int u = 0; u < NT; ++u)
             mx = fmaxf(mx, fmaxf(fmaxf(xs[u][0], xs[u][1]), fmaxf(xs[u][2], xs[u][3])));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        if constexpr (PK) mx = fmaxf(mx, half_row(mx));
+        mx = rows_max(mx);
         const float ms = mx == -INFINITY ? 0.0f : mx;
         float ls = 0.0f;
-        float* rbw = sm.rowbuf + ((size_t)(row % kRowBufs) * G + h) * kTs + wtok0 + 4 * g;
+        float* rbw = sm.rowbuf + ((size_t)(row % kRowBufs) * G + hc) * kTs + wtok0 + 16 * ub + 4 * g;
 #pragma unroll
-        for (int u = 0; u < KT; ++u) {
+        for (int u = 0; u < NT; ++u) {
             f32x4 pv;
 #pragma unroll
             for (int i = 0; i < 4; ++i) pv[i] = hw_exp2(xs[u][i] - ms);
             ls += (pv[0] + pv[1]) + (pv[2] + pv[3]);
-            if (h < G) *reinterpret_cast<f32x4*>(rbw + 16 * u) = pv;
+            if (hc < G) *reinterpret_cast<f32x4*>(rbw + 16 * u) = pv;
         }
-        load_tile(ring[3], row + 2, 3);
-        ls += __shfl_xor(ls, 16);
-        ls += __shfl_xor(ls, 32);
+        load_tile(ring[3], 3);
+        next_row(row + 3);
+        if constexpr (PK) ls += half_row(ls);
+        ls = rows_sum(ls);
         after_tiles(row);
         if (g == 0 && h < kSlots) wm_wave[(size_t)(row % kRowBufs) * W * kSlots + h] = ms;
         if (g == 0 && h < G) sm.wstat[((row & 1) * W + wv) * 16 + h] = make_float2(mx, ls);
@@ -694,7 +807,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // drain, so that the lane's other workgroups find it published as they
     // finish (claimed after the drain, they waited for it about 10 us)
     if (next_box != nullptr) {
-        claim_sessions(a, sm.claim, claim_lane, cap);
+        claim_sessions(sm.claim, claim_lane, cap);
         if (threadIdx.x == 0) {
             __hip_atomic_store(next_box,
                                ((unsigned long long)tag << 32) | ((uint32_t)sm.claim[0] << 16) | (uint32_t)sm.claim[1],
@@ -780,12 +893,18 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // Every load first, then the stores: a wait for a load also waits for
     // the stores issued before it.  The session's region priors are read
     // once per wave (lane r holds region r's) and picked by shuffles.
-    const int t_now = a.clock[un.s];
-    const size_t rbase = (size_t)un.s * dm.n_regions;
-    const float b_l = lane < dm.n_regions ? a.b[rbase + lane] : 0.0f;
-    const float lam_l = lane < dm.n_regions ? a.lam[rbase + lane] : 0.0f;
+    const auto* const ce = cold_args();
+    const auto* const cd = cold_dims();
+    const auto imp = global(ce->imp), abar_out = global(ce->abar_out);
+    const auto t_ref = global(ce->t_ref);
+    const auto region = global(ce->region);
+    const int n_regions = cd->n_regions;
+    const int t_now = global(ce->clock)[un.s];
+    const size_t rbase = (size_t)un.s * n_regions;
+    const float b_l = lane < n_regions ? global(ce->b)[rbase + lane] : 0.0f;
+    const float lam_l = lane < n_regions ? global(ce->lam)[rbase + lane] : 0.0f;
     const int n_tok = AL ? un.nl_s : un.nt_s;   // |K_t|
-    const float aw = attention_weight(dm.alpha, dm.norm_attn, n_tok);
+    const float aw = attention_weight(cd->alpha, cd->norm_attn, n_tok);
     bool live[kTok];
     size_t si[kTok];
     float a_old[kTok];
@@ -802,39 +921,39 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         a_old[k] = 0.0f;
         tr_old[k] = reg[k] = 0;
         if (live[k]) {
-            a_old[k] = a.imp[si[k]];
-            tr_old[k] = a.t_ref[si[k]];
-            reg[k] = a.region[si[k]];
+            a_old[k] = imp[si[k]];
+            tr_old[k] = t_ref[si[k]];
+            reg[k] = region[si[k]];
         }
     }
 #pragma unroll
     for (int k = 0; k < kTok; ++k) {
         const int lt = lane + 64 * k;
         int r = reg[k];
-        if (live[k] && r >= dm.n_regions) {
+        if (live[k] && r >= n_regions) {
             atomicOr(a.status, kDevCorrupt);
-            r = dm.n_regions - 1;
+            r = n_regions - 1;
         }
         const float br = __shfl(b_l, r), lamr = __shfl(lam_l, r);
         float sc = 0.0f;
         bool pin = false;
         if (live[k]) {
-            const float abar = acc[k] / (float)dm.R;
-            const float an = fmaf(dm.rho, a_old[k], (1.0f - dm.rho) * abar);
-            a.imp[si[k]] = an;
+            const float abar = acc[k] / (float)cd->R;
+            const float an = fmaf(cd->rho, a_old[k], (1.0f - cd->rho) * abar);
+            imp[si[k]] = an;
             int tr = tr_old[k];
-            if (abar >= dm.tau_scale / (float)n_tok) {
+            if (abar >= cd->tau_scale / (float)n_tok) {
                 tr = t_now;
-                a.t_ref[si[k]] = tr;
+                t_ref[si[k]] = tr;
             }
-            if (a.abar_out != nullptr) a.abar_out[si[k]] = abar;
-            pin = (dm.pin_mask >> r) & 1u;
+            if (abar_out != nullptr) abar_out[si[k]] = abar;
+            pin = (cd->pin_mask >> r) & 1u;
             sc = pin ? INFINITY : retention_score(br, lamr, t_now, tr, aw, an);
         }
         float ps;
         const bool has = page_score_of(sc, live[k], pin, dm.P, &ps);
         const int tok = un.j * kT + wtok0 + lt;
-        if ((lt & (dm.P - 1)) == 0 && has) a.pscore[(size_t)un.s * dm.MP + (tok >> dm.Pshift)] = ps;
+        if ((lt & (dm.P - 1)) == 0 && has) global(ce->pscore)[(size_t)un.s * dm.MP + (tok >> dm.Pshift)] = ps;
     }
 }
 
@@ -871,12 +990,15 @@ __device__ int count_at_most(const int32_t* v, int n, int x, int* tmp) {
 // back (lane 1), by compare-and-swap on the (first, end) word.  Writes the
 // claimed [first, end) to xs[0], xs[1] (both 0 when nothing is left).
 // Whole workgroup; contains barriers.
-__device__ void claim_sessions(const AttendArgs& a, int* xs, int lane_no, int cap) {
+__device__ void claim_sessions(int* xs, int lane_no, int cap) {
     const bool front = (lane_no & 1) == 0;
+    const auto* const ca = cold_args();
+    unsigned long long* const claim = ca->claim;
+    const int32_t* const ustart = ca->ustart;
     int* tmp = xs + 2;
     while (true) {
         if (threadIdx.x == 0) {
-            const unsigned long long c = __hip_atomic_load(a.claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long c = __hip_atomic_load(claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             xs[4 + 17] = (int)(c >> 32);
             xs[5 + 17] = (int)(c & 0xffffffffu);
         }
@@ -892,7 +1014,7 @@ __device__ void claim_sessions(const AttendArgs& a, int* xs, int lane_no, int ca
         // unless some have no units, and then the next pass takes the rest)
         const int t = (int)threadIdx.x;
         const int s = front ? f + t : e - 1 - t;
-        const int u = (t < e - f) ? a.ustart[s + 1] - a.ustart[s] : (cap + 1);
+        const int u = (t < e - f) ? ustart[s + 1] - ustart[s] : (cap + 1);
         int tot;
         const int before = block_exclusive_scan(u, tmp, &tot);
         const bool take = t < e - f && before + u <= cap;
@@ -901,7 +1023,7 @@ __device__ void claim_sessions(const AttendArgs& a, int* xs, int lane_no, int ca
             const int nf = front ? f + k : f, ne = front ? e : e - k;
             const unsigned long long want = ((unsigned long long)(uint32_t)nf << 32) | (uint32_t)ne;
             const unsigned long long seen = ((unsigned long long)(uint32_t)f << 32) | (uint32_t)e;
-            const unsigned long long got = atomicCAS(a.claim, seen, want);
+            const unsigned long long got = atomicCAS(claim, seen, want);
             xs[4 + 17] = got == seen;
             xs[0] = front ? f : e - k;
             xs[1] = front ? f + k : e;
@@ -965,17 +1087,18 @@ k_attend(AttendDims dm, AttendArgs a) {
         lds_sync();   // the previous unit is done with the LDS
         if (threadIdx.x == 0) *sm.vflag = 0;   // ordered before the unit by the barriers below
         int sb, se;
+        const auto* const cp = cold_args();
         if (!lanes) {
             if (ps >= n_pass) break;
-            sb = a.plan[2 + 3 * ps];
-            se = a.plan[3 + 3 * ps];
+            sb = cp->plan[2 + 3 * ps];
+            se = cp->plan[3 + 3 * ps];
         } else {
             // the lane's first workgroup claimed this pass during its last
             // unit (unless that pass gave it no unit)
             const bool ahead = w == 0 && ps > 0 && sm.claim[24] != 0;
-            if (w == 0 && ps > 0 && !ahead) claim_sessions(a, xs, lane_no, cap);
+            if (w == 0 && ps > 0 && !ahead) claim_sessions(xs, lane_no, cap);
             if (threadIdx.x == 0) {
-                unsigned long long* box = a.lane_box + (size_t)lane_no * (dm.S + 1) + ps;
+                unsigned long long* box = cp->lane_box + (size_t)lane_no * (dm.S + 1) + ps;
                 if (ahead) {
                     xs[0] = sm.claim[0];
                     xs[1] = sm.claim[1];
@@ -989,7 +1112,7 @@ k_attend(AttendDims dm, AttendArgs a) {
                     unsigned long long v = __hip_atomic_load(box, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     while ((uint32_t)(v >> 32) != tag) {
                         if (now_ticks() - t0 > kUnitTicks) {
-                            atomicOr(a.status, MD_DEV_TIMEOUT);
+                            atomicOr(cp->status, MD_DEV_TIMEOUT);
                             v = 0;
                             break;
                         }
@@ -1006,20 +1129,20 @@ k_attend(AttendDims dm, AttendArgs a) {
             if (threadIdx.x == 0 && ahead) sm.claim[24] = 0;   // read by all threads before the barrier above
             if (sb >= se) break;
         }
-        const int u0 = a.ustart[sb];
-        if (w >= a.ustart[se] - u0) continue;
+        const int u0 = cp->ustart[sb];
+        if (w >= cp->ustart[se] - u0) continue;
         // session of unit u0 + w: the last s in [sb, se) with ustart[s] <= u0 + w
-        const int s = sb + count_at_most(a.ustart + sb, se - sb, u0 + w, xs + 2) - 1;
+        const int s = sb + count_at_most(cp->ustart + sb, se - sb, u0 + w, xs + 2) - 1;
         Unit un;
         un.s = s;
-        un.us = uni(a.ustart[s]);
-        un.nu = uni(a.ustart[s + 1]) - un.us;
+        un.us = uni(cp->ustart[s]);
+        un.nu = uni(cp->ustart[s + 1]) - un.us;
         un.j = u0 + w - un.us;
         // the session's units are rg groups of nu / rg units, group g
         // covering rows [g L Hkv / rg, (g + 1) L Hkv / rg)
-        const int rg = min(max(uni(a.rgs[s]), 1), kMaxRowGroups);
+        const int rg = min(max(uni(cp->rgs[s]), 1), kMaxRowGroups);
         const int nut = max(un.nu / rg, 1);
-        if (un.nu != nut * rg && threadIdx.x == 0) atomicOr(a.status, kDevCorrupt);
+        if (un.nu != nut * rg && threadIdx.x == 0) atomicOr(cp->status, kDevCorrupt);
         un.rg = rg;
         un.ubase = un.us;
         un.grp = min(un.j / nut, rg - 1);
@@ -1028,8 +1151,8 @@ k_attend(AttendDims dm, AttendArgs a) {
         un.us += un.grp * nut;
         un.r0 = un.grp * dm.LHkv / rg;
         un.r1 = (un.grp + 1) * dm.LHkv / rg;
-        un.nt_s = a.n_tokens[s];
-        un.nl_s = AL ? a.n_live[s] : 0;
+        un.nt_s = cp->n_tokens[s];
+        un.nl_s = AL ? cp->n_live[s] : 0;
         constexpr int kT = 16 * W * KT;
         un.ntok = min(kT, un.nt_s - un.j * kT);
         un.deadline = now_ticks() + kUnitTicks;
@@ -1038,7 +1161,7 @@ k_attend(AttendDims dm, AttendArgs a) {
         int lane = (int)threadIdx.x & 63;
         asm volatile("" : "+v"(lane));
         unsigned long long* next_box =
-            (lanes && w == 0) ? a.lane_box + (size_t)lane_no * (dm.S + 1) + ps + 1 : nullptr;
+            (lanes && w == 0) ? cold_args()->lane_box + (size_t)lane_no * (dm.S + 1) + ps + 1 : nullptr;
         attend_wave<W, NH, KT, AL, QT, WN>(dm, a, sm, un, wv, lane, tag, lane_no, cap, next_box);
     }
 }
