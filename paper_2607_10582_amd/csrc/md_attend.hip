@@ -16,8 +16,8 @@
 // its tokens' mass.  The key cache is read once and nothing per
 // (token, row) is written back.
 //
-// Workgroup = four waves with the same job; wave w owns the unit's tiles
-// 4w .. 4w + 3 (16 tokens each), i.e. tokens 64w .. 64w + 63.  Each wave
+// Workgroup = four waves with the same job; wave w of unit j (of nu) owns
+// the session's chunk j + w nu of 64 tokens, four tiles of 16.  Each wave
 // streams its K tiles through registers two rows ahead of the row it works
 // on, so its loads never wait for a row boundary.
 // At a row boundary the waves meet once (s_barrier, no memory fence: a fence
@@ -25,11 +25,11 @@
 //   * every wave merges its own (max, sum) of the row into LDS; after the
 //     barrier, wave w merges the four partials of heads w, w + 4, ... and
 //     publishes them for the other units;
-//   * wave w also gathers every unit's statistics of heads w, w + 4, ... of
-//     the row kConsumeLag back (the loads go out at one barrier and are used
-//     in the next row, after loads that the ring does not wait for) and
-//     writes that row's normalisers to LDS before the next barrier; the row
-//     is normalised in the row after that;
+//   * for the rows it leads (every nu-th), the unit gathers every unit's
+//     statistics and publishes the row's normalisers, wave w those of heads
+//     w, w + 4, ...;
+//   * one wave (in turn) reads the normalisers of the row to be normalised
+//     next and writes them to LDS before the next barrier;
 //   * wave w stages its quarter of the query of the next row (three bf16
 //     terms per float, loaded at the last barrier).
 // All of it but the barrier runs between the tiles of the following row.
@@ -227,7 +227,7 @@ __device__ __forceinline__ float half_row(float v) {
 }
 
 struct Unit {
-    int s, j, ntok, nt_s, nu, us;
+    int s, j, nt_s, nu, us;
     uint64_t deadline;   // real-time tick after which the unit stops waiting
     int nl_s;            // region-aligned pages: the session's tokens |K_t| (nt_s counts holes too)
     // row groups: the unit covers rows [r0, r1) of group grp of rg; nu, j
@@ -274,11 +274,17 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     const int hc = PK ? h & 7 : h;         // the lane's query head of the group
     const int ub = PK ? (h >> 3) * NT : 0; // its first tile
     const int hh = min(hc, G - 1);         // in-bounds head for the unused columns
-    const uint32_t voff = 16u * lane;   // piece (8-dim block 4j + g, token h) of a 16-token block
     constexpr int kT = 16 * W * KT;   // tokens per unit
     constexpr int kTs = tstride(W, KT);
     constexpr int kTok = KT / 4;          // tokens per lane
     const int wtok0 = wv * 16 * KT;       // unit-local token of this wave's first tile
+    // The session's tokens go to its units in chunks of a wave's 64, wave w of
+    // unit j taking chunk j + w nu: the units wait for each other in every
+    // row, and neighbouring tokens are alike in what they cost (the pinned
+    // span of a quantised session stays bf16, twice the bytes).  16 sessions
+    // of 8,192 tokens, 1,024 of each pinned: 281 us a step against 315 with
+    // units of 256 neighbouring tokens; bf16 alone unchanged.
+    const int tok0 = (un.j + un.nu * wv) * 16 * KT;
     bool dead = false;                    // a wait of this wave ran out: stop waiting
     // the unit's rows [r_beg, r_end)
     const int r_beg = un.r0, r_end = un.r1;
@@ -287,7 +293,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     int myslot = 0;
     bool myok = false;
     if (lane < KT) {
-        const int tok = un.j * kT + wtok0 + 16 * lane;
+        const int tok = tok0 + 16 * lane;
         if (tok < un.nt_s) {
             const int p = a.page_table[(size_t)un.s * dm.MP + (tok >> dm.Pshift)];
             if ((unsigned)p < (unsigned)dm.NP) {
@@ -332,7 +338,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
             const int slot = WN ? __shfl(myslot, t) : 0;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                bool no = !ok || wtok0 + 16 * t + 4 * g + i >= un.ntok;
+                bool no = !ok || tok0 + 16 * t + 4 * g + i >= un.nt_s;
                 if constexpr (AL) no |= 4 * g + i >= (int)((lims >> (8 * t)) & 0xffu);
                 if constexpr (WN) no |= ok && a.t_ins[slot + 4 * g + i] > t_lim;
                 gone |= no ? 1u << (4 * u + i) : 0u;
@@ -350,26 +356,38 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
 
     // K tile u of a row in the MFMA A layout: the pool keeps each block of
     // 16 tokens as [d / 8][16][8], so load j reads 1 KiB contiguous and lane
-    // (h, g) gets token h's dims 32j + 8g .. +7.  A tile without cached
-    // tokens, or past the last row, reads the pool's first tile (its logits
-    // are masked), so loads never branch.  Lane u < KT keeps tile u's address
-    // in the row to load next and moves it on once per row (next_row): two
-    // register reads per tile in place of its address from the row number.
+    // (h, g) gets token h's dims 32j + 8g .. +7.  Lane u < KT keeps tile u's
+    // address in the row to load next and moves it on once per row
+    // (next_row): two register reads per tile in place of its address from
+    // the row number.  Loads never branch: those of a tile without cached
+    // tokens, or past the last row, all go to the first 16 bytes of each KiB
+    // of a tile the unit holds anyway (its first, or the last row's).  Were
+    // they to read one whole tile of the pool, the same for every unit, that
+    // tile's few channels would answer late: a session's last unit, mostly
+    // empty, then ran slower than all others, and they waited for it in
+    // every row.
     const uint64_t pool = reinterpret_cast<uint64_t>(a.k_pool);
     uint64_t kaddr = pool;
-    uint32_t kstep = 0;
-    if (myok) {
-        kaddr = pool + (((size_t)(myslot >> dm.Pshift) * dm.LHkv + r_beg) * dm.P + (myslot & (dm.P - 1))) *
+    const uint32_t kstep = (uint32_t)dm.P * (kHeadDim * sizeof(uint16_t));
+    uint32_t reads = (uint32_t)(vmask & kAll);   // tiles whose loads read their lanes' own pieces
+    {
+        int slot = myslot;
+        if (!myok) {   // the unit's first tile, if that has a page
+            const int p = a.page_table[(size_t)un.s * dm.MP + ((un.j * 16 * KT) >> dm.Pshift)];
+            slot = (unsigned)p < (unsigned)dm.NP ? p << dm.Pshift : 0;
+        }
+        kaddr = pool + (((size_t)(slot >> dm.Pshift) * dm.LHkv + r_beg) * dm.P + (slot & (dm.P - 1))) *
                            (kHeadDim * sizeof(uint16_t));
-        kstep = (uint32_t)dm.P * (kHeadDim * sizeof(uint16_t));
     }
     auto next_row = [&](int r) {   // the tiles of row r are loaded next
-        kaddr = r < r_end ? kaddr + kstep : pool;
+        if (r < r_end) kaddr += kstep; else reads = 0;
     };
     auto load_tile = [&](u32x4 (&rg)[4], int u) {
         const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)kaddr, u);
         const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(kaddr >> 32), u);
         gbytes base = (gbytes)(((uint64_t)hi << 32) | lo);
+        const uint32_t own = ((reads >> u) & 1u) ? ~0u : 0u;
+        const uint32_t voff = 16u * lane & own;   // piece (8-dim block 4j + g, token h) of a 16-token block
         if constexpr (QT) {
             // a quantised block: codes in its first 2 KiB (rg[0], rg[1]), the
             // scale at byte 2048 (rg[2]); rg[3] takes the next 16 bytes of
@@ -472,20 +490,15 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         }
     };
 
-    // Normaliser words of row x: wave x mod 4 reads them (lane h: head h)
-    // and, once they carry the tag, writes them to LDS.
+    // Normaliser words of row x (lane h: head h).  Every wave reads them for
+    // itself: handed on through LDS they would have to be there a row
+    // earlier, at the barrier before the row that uses them.
     const bool hd_lane = lane < NH && wv + W * lane < G;
     unsigned long long nw[2];
     auto load_norm = [&](int x) {
         const unsigned long long* p = norm_word(x, min(lane, G - 1));
         nw[0] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         nw[1] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto check_norm = [&](int x) {
-        await_tags([&] { return lane >= G || (tag_ok(nw[0]) && tag_ok(nw[1])); }, [&] { load_norm(x); });
-        if (lane < G)
-            sm.norm[(x & 1) * 16 + lane] =
-                make_float2(__uint_as_float((uint32_t)nw[0]), __uint_as_float((uint32_t)nw[1]));
     };
 
     // Leader: the units' words of heads wv + W i, lane k = unit k (the first
@@ -591,14 +604,20 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     // registers and push the quantised and window instantiations into spills.
     constexpr int kSlots = W * NH;
     float* const wm_wave = sm.wmax + (size_t)wv * kSlots;
+    auto check_norm = [&](int x) {
+        await_tags([&] { return tag_ok(nw[0]) && tag_ok(nw[1]); }, [&] { load_norm(x); });
+        if (lane < G)
+            sm.norm[(x & 1) * 16 + lane] =
+                make_float2(__uint_as_float((uint32_t)nw[0]), __uint_as_float((uint32_t)nw[1]));
+    };
     auto consume = [&](int x) {
         const float* rb = sm.rowbuf + (size_t)(x % kRowBufs) * G * kTs + wtok0 + lane;
         const float mw = wm_wave[(size_t)(x % kRowBufs) * W * kSlots + min(h, kSlots - 1)];
-        const float2 n = sm.norm[(x & 1) * 16 + hh];
-        const float f = h < G ? hw_exp2(mw - n.x) * n.y : 0.0f;
+        const float2 n = sm.norm[(x & 1) * 16 + min(h, G - 1)];
+        const float fw = h < G ? hw_exp2(mw - n.x) * n.y : 0.0f;
 #pragma unroll
         for (int hd = 0; hd < W * NH; ++hd) {   // heads past the group read a valid row and weigh zero
-            const float fh = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), hd));
+            const float fh = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fw), hd));
 #pragma unroll
             for (int k = 0; k < kTok; ++k) acc[k] = fmaf(rb[min(hd, G - 1) * kTs + 64 * k], fh, acc[k]);
         }
@@ -606,33 +625,40 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
 
     // Bookkeeping of iteration r (a row of tiles for r < LHkv, then
     // kConsumeLag iterations without tiles).  Row x's words travel:
-    //   iteration x + 1  its unit statistics are published;
-    //   iteration x + 3  the leader requests them (a row and a half after the
-    //                    last unit can have published);
+    //   iteration x + 1  its unit statistics are published, right after the
+    //                    row's MFMA;
+    //   iteration x + 3  the leader requests them, two rows later;
     //   iteration x + 4  the leader publishes the normalisers;
-    //   iteration x + 5  every unit requests them;
+    //   iteration x + 5  one wave of every unit requests them;
     //   iteration x + 6  they go to LDS, before the barrier;
     //   iteration x + 7  row x's held logits are normalised.
     // Requests are the loads of iteration r: they go out before the tiles of
     // row r + 2 and are used at iteration r + 1, after the tiles of row
     // r + 1 came in, so no wait ever holds the tile loads up (loads come back
-    // in issue order).
+    // in issue order).  A word that is not there yet costs more than its own
+    // round trip: the request sent again comes back after every tile in
+    // flight.  So what others wait for goes first in an iteration, and one
+    // wave alone asks for the normalisers while the others keep their tiles
+    // in flight (every wave asking for itself a row later, without the way
+    // through LDS, measured slower: 64 sessions of 439,000 tokens 1,290
+    // against 1,269 us a step, prompts of 16 x 32,768 tokens 1,379 against
+    // 1,325; published after the row's softmax instead 1,275 and 1,331).
     auto use_loads = [&](int r) {   // steps of iteration r that use iteration r - 1's loads
-        const int xa = r - 6;
-        if (xa >= r_beg && xa <= last && (xa & (W - 1)) == wv) check_norm(xa);
+        if (r - 1 >= r_beg && r - 1 <= last) publish(r - 1);
         if (lead_now) lead(r - 4);
+        const int xf = r - (kConsumeLag - 1);
+        if (xf >= r_beg && xf <= last && (xf & (W - 1)) == wv) check_norm(xf);
     };
     auto issue_loads = [&](int r) {
-        if (((r - 5) & (W - 1)) == wv) load_norm(min(max(r - 5, r_beg), last));
         const int xd = r - 3;
         lead_now = xd == lead_next && xd <= last;
         if (lead_now) {
             load_stats(xd, 0);
             lead_next += un.nu;
         }
+        if (((r - (kConsumeLag - 2)) & (W - 1)) == wv) load_norm(min(max(r - (kConsumeLag - 2), r_beg), last));
     };
-    auto after_tiles = [&](int r) {   // publish row r - 1, normalise row r - 7
-        if (r - 1 >= r_beg && r - 1 <= last) publish(r - 1);
+    auto after_tiles = [&](int r) {   // normalise row r - 7
         const int xf = r - kConsumeLag;
         if (xf >= r_beg && xf <= last) consume(xf);
     };
@@ -651,7 +677,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
 #pragma unroll
     for (int u = 0; u < KT; ++u) load_tile(ringA[u], u);
     next_row(r_beg + 1);
-    if (((r_beg - 5) & (W - 1)) == wv) load_norm(r_beg);
+    load_norm(r_beg);
     load_q(min(r_beg + 1, last));
 #pragma unroll
     for (int u = 0; u < KT; ++u) load_tile(ringB[u], u);
@@ -661,10 +687,11 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     //   1. logits of the four tiles on MFMA, k-chunk by k-chunk (the chunk's
     //      query terms are read from LDS once, the four accumulations run
     //      side by side);
-    //   2. bookkeeping on the last iteration's loads; the query of row r + 1
-    //      into LDS; this iteration's requests and row r + 2's query;
+    //   2. publish row r - 1; bookkeeping on the last iteration's loads; the
+    //      query of row r + 1 into LDS; this iteration's requests and row
+    //      r + 2's query;
     //   3. softmax statistics of row r, its logits into LDS;
-    //   4. publish row r - 1, normalise row r - 7; row r's statistics into
+    //   4. normalise row r - 7; row r's statistics into
     //      LDS; barrier.
     // The four tiles of row r + 2 go out one by one between these steps
     // rather than in one burst: a burst of all waves' loads at once stalls
@@ -915,7 +942,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         const int tile = lt >> 4;
         const int slot0 = __shfl(myslot, tile);
         // holes hold no token
-        live[k] = wtok0 + lt < un.ntok && ((vmask >> tile) & 1ull) &&
+        live[k] = tok0 + lt < un.nt_s && ((vmask >> tile) & 1ull) &&
                   (!AL || (lt & 15) < (int)((lims >> (8 * tile)) & 0xffu));
         si[k] = (size_t)slot0 + (lt & 15);
         a_old[k] = 0.0f;
@@ -952,7 +979,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         }
         float ps;
         const bool has = page_score_of(sc, live[k], pin, dm.P, &ps);
-        const int tok = un.j * kT + wtok0 + lt;
+        const int tok = tok0 + lt;
         if ((lt & (dm.P - 1)) == 0 && has) global(ce->pscore)[(size_t)un.s * dm.MP + (tok >> dm.Pshift)] = ps;
     }
 }
@@ -1153,8 +1180,6 @@ k_attend(AttendDims dm, AttendArgs a) {
         un.r1 = (un.grp + 1) * dm.LHkv / rg;
         un.nt_s = cp->n_tokens[s];
         un.nl_s = AL ? cp->n_live[s] : 0;
-        constexpr int kT = 16 * W * KT;
-        un.ntok = min(kT, un.nt_s - un.j * kT);
         un.deadline = now_ticks() + kUnitTicks;
         // The lane index is made opaque here so that per-lane address
         // arithmetic is not hoisted out of the pass loop and kept live.

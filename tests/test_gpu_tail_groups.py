@@ -26,7 +26,7 @@ def _need_gpu():
     B.load_library()
 
 
-def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, quant=0.0):
+def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, quant=0.0, fused=True):
     """Two steps over sessions of `tokens` tokens; the same inputs for every
     setting of row_groups.  Budgets keep every token, so slots line up."""
     gen = torch.Generator(device="cuda").manual_seed(11)
@@ -43,7 +43,7 @@ def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, qua
         at += pages[s]
     cache.set_free_pages(ids[at:])
     md = MemDecay(cache, torch.full((S, 7), 0.5), torch.full((S, 7), 0.01), rho=0.9, alpha=1.0, tau_scale=2.0,
-                  pinned_mask=1, fused=True, window=window, region_aligned=aligned, quant_threshold=quant,
+                  pinned_mask=1, fused=fused, window=window, region_aligned=aligned, quant_threshold=quant,
                   row_groups=row_groups)
     abar = torch.zeros((cache.n_phys, P), device="cuda")
     out = []
