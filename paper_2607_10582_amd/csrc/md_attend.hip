@@ -387,7 +387,14 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(kaddr >> 32), u);
         gbytes base = (gbytes)(((uint64_t)hi << 32) | lo);
         const uint32_t own = ((reads >> u) & 1u) ? ~0u : 0u;
-        const uint32_t voff = 16u * lane & own;   // piece (8-dim block 4j + g, token h) of a 16-token block
+        uint32_t voff = 16u * lane & own;   // piece (8-dim block 4j + g, token h) of a 16-token block
+        if constexpr (AL && !QT) {
+            // a hole's lanes repeat the last token's piece: a tile of up to
+            // eight tokens then takes half of its lines (16 sessions of 8,192
+            // tokens, two fifths of them in turns of 24: 382 to 352 us a step)
+            const int lim = (int)((lims >> (8 * u)) & 0xffu);
+            voff = 16u * ((lane & 48) + max(min(h, lim - 1), 0)) & own;
+        }
         if constexpr (QT) {
             // a quantised block: codes in its first 2 KiB (rg[0], rg[1]), the
             // scale at byte 2048 (rg[2]); rg[3] takes the next 16 bytes of
