@@ -146,7 +146,7 @@ struct Scratch {
     int32_t* recall;       // [S][H] offload tier: the listed page is recalled at this step
     int32_t* rcount;       // [S] pages each session recalls at this step
     int32_t* rows_done;    // [S] session kernel: row ranges done (low half), void ranges (high half)
-    int32_t* rows_read;    // [1] session kernel: workgroups that have read the step's counters
+    int32_t* rows_read;    // [1] session kernel: workgroups that have read the step's counters (0 between launches)
     float* rows_part;      // [S][ranges][rows_capacity] session kernel: partial masses
 };
 

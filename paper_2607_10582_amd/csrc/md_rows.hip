@@ -11,15 +11,18 @@
 // The mass of a token sums over rows (Sec. III-C), so the row ranges' partial
 // masses go to scratch, and the workgroup that finishes a session last adds
 // them in range order and runs the epilogue (Eq. 2 - 5) for its tokens.
-// Nothing waits for a workgroup that may not have started, so the grid needs
-// no residency.
+// No workgroup waits for another one, so the grid needs no residency.
 //
 // The append (Fig. 1) runs in the same launch: every workgroup works out its
 // session's new token from the counters as they stand before the step, reads
 // its key from new_k in place of the pool, and writes its own rows of it to
 // the pool; the workgroup that finishes the session writes the token's state.
-// One more workgroup, the last, commits the counters, page tables and the
-// free list once every other one has said that it has read them.
+// The counters, page tables and the free list are committed by whichever
+// workgroup is the last to have read them, as a count of arrivals tells
+// (md_arrive.h).  One more workgroup, dispatched last, has no rows: it works
+// the commit out while the others read, and as a rule arrives last and
+// commits under their rows; if it does not, the last of the others commits
+// when it is done.
 //
 // What bounds it: for a single session of a few hundred tokens the chain of
 // dependent memory round trips (counters and page table, keys, partial
@@ -27,6 +30,7 @@
 
 #include <algorithm>
 
+#include "md_arrive.h"
 #include "md_device.h"
 
 namespace md {
@@ -128,13 +132,14 @@ __device__ __forceinline__ Append append_of(const Dims& dm, const View& v, int s
     return a;
 }
 
-// The last workgroup: the counters, page tables and the free list after the
-// append, and the scoring kernel's work list, written once every other
-// workgroup has read the old ones.
-__device__ void rows_commit(const Dims& dm, const View& v, const Scratch& sc, const uint16_t* new_k,
-                            const uint8_t* new_region) {
+// The commit: the counters, page tables and the free list after the append,
+// and the scoring kernel's work list.  Whole workgroup.  The workgroup without
+// rows (early) arrives once it has worked them out, and leaves them to a
+// later one if it is not the last; any other comes here as the last.
+__device__ __forceinline__ void rows_commit(const Dims& dm, const View& v, const Scratch& sc, const uint16_t* new_k,
+                                            const uint8_t* new_region, bool early) {
     __shared__ int lds[3 * 17];
-    __shared__ int sh_go;
+    __shared__ int sh_mine;
     const int tid = threadIdx.x;
     constexpr int kPer = kMaxSessions / kRT;
     const int fc = v.free_count[0];
@@ -178,20 +183,13 @@ __device__ void rows_commit(const Dims& dm, const View& v, const Scratch& sc, co
     const int m[2] = {tiles, tokens};
     int ex[2], tot[2];
     block_exclusive_scan_n<2>(m, lds, ex, tot);
-    if (tid == 0) {
-        const int others = (int)gridDim.x - 1;
-        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-        int seen = load_agent(sc.rows_read);
-        while (seen < others && __builtin_amdgcn_s_memrealtime() - t0 < kWordWaitTicks) {
-            __builtin_amdgcn_s_sleep(2);
-            seen = load_agent(sc.rows_read);
-        }
-        sh_go = seen >= others;
-        if (!sh_go) atomicOr(sc.status, kDevCorrupt | MD_DEV_TIMEOUT);
-        else *sc.rows_read = 0;
+    if (early) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the old counters are in registers
+        lds_sync();
+        if (tid == 0) sh_mine = arrive_last(sc.rows_read, arrive(sc.rows_read), (int)gridDim.x);
+        lds_sync();
+        if (!sh_mine) return;
     }
-    __syncthreads();
-    if (!sh_go) return;   // cannot happen: the other workgroups started before this one
     int st = 0;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
@@ -223,18 +221,15 @@ __device__ void rows_commit(const Dims& dm, const View& v, const Scratch& sc, co
     }
 }
 
-// GS: head slots (4, 8 or 16 >= G, the MFMA columns: query heads per KV head
-// times window queries); QT: quantised tier; WN: window of several queries.
+// One workgroup's rows of its session, and the session's tokens if it
+// finishes them last.  Returns whether the commit is this workgroup's.
 template <int GS, bool QT, bool WN>
-__global__ void __launch_bounds__(kRT) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_rows(Dims dm, View v, Scratch sc, const float* __restrict__ q, const uint16_t* __restrict__ new_k,
-       const uint8_t* __restrict__ new_region, float* abar_out, int rg, int nc_cap) {
-    if (blockIdx.x == gridDim.x - 1) {
-        rows_commit(dm, v, sc, new_k, new_region);
-        return;
-    }
+__device__ __forceinline__ bool rows_work(const Dims& dm, const View& v, const Scratch& sc,
+                                          const float* __restrict__ q, const uint16_t* __restrict__ new_k,
+                                          const uint8_t* __restrict__ new_region, float* abar_out, int rg,
+                                          int nc_cap) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int sh_rank, sh_bad, sh_old;
+    __shared__ int sh_rank, sh_bad, sh_old, sh_commit;
     const int tid = threadIdx.x, lane = lane_id();
     const int wv = uni(tid >> 6);
     const int s = (int)blockIdx.x / rg, grp = (int)blockIdx.x - s * rg;
@@ -282,10 +277,12 @@ k_rows(Dims dm, View v, Scratch sc, const float* __restrict__ q, const uint16_t*
     const int n_old = ap.ok ? nt0 : 0;         // tokens (and holes) before the append
     const int tok_new = ap.app ? n - 1 : -1;
 
-    // every counter this workgroup needs is in registers: say so
+    // every counter this workgroup needs is in registers: say so (the count
+    // before it is looked at when the rows are done, so nothing waits for it)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_sync();
-    if (tid == 0) atomicAdd(sc.rows_read, 1);
+    int arrived = 0;
+    if (tid == 0) arrived = arrive(sc.rows_read);
 
     // ---- tiles
     int myslot = 0;
@@ -574,9 +571,11 @@ k_rows(Dims dm, View v, Scratch sc, const float* __restrict__ q, const uint16_t*
         if (sh_bad) atomicOr(sc.status, MD_DEV_NONFINITE);
         sh_old = __hip_atomic_fetch_add(sc.rows_done + s, 1 + (sh_bad ? 1 << 16 : 0), __ATOMIC_RELAXED,
                                         __HIP_MEMORY_SCOPE_AGENT);
+        sh_commit = arrive_last(sc.rows_read, arrived, (int)gridDim.x);
     }
     lds_sync();
-    if ((sh_old & 0xffff) != rg - 1) return;
+    const bool commit = sh_commit != 0;
+    if ((sh_old & 0xffff) != rg - 1) return commit;
     const bool is_void = (sh_old >> 16) != 0 || sh_bad != 0;
     if (tid == 0) {
         sc.rows_done[s] = 0;
@@ -676,6 +675,18 @@ k_rows(Dims dm, View v, Scratch sc, const float* __restrict__ q, const uint16_t*
         const bool has = page_score_of(sci, live, pin, dm.P, &ps);
         if ((lane & (dm.P - 1)) == 0 && has && !is_void) sc.pscore[(size_t)s * dm.MP + tp] = ps;
     }
+    return commit;
+}
+
+// GS: head slots (4, 8 or 16 >= G, the MFMA columns: query heads per KV head
+// times window queries); QT: quantised tier; WN: window of several queries.
+template <int GS, bool QT, bool WN>
+__global__ void __launch_bounds__(kRT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_rows(Dims dm, View v, Scratch sc, const float* __restrict__ q, const uint16_t* __restrict__ new_k,
+       const uint8_t* __restrict__ new_region, float* abar_out, int rg, int nc_cap) {
+    const bool rowless = blockIdx.x == gridDim.x - 1;
+    if (!rowless && !rows_work<GS, QT, WN>(dm, v, sc, q, new_k, new_region, abar_out, rg, nc_cap)) return;
+    rows_commit(dm, v, sc, new_k, new_region, rowless);
 }
 
 template <bool QT, bool WN>

@@ -30,15 +30,16 @@ from collections import defaultdict
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
-KERNEL_SOURCES = {"k_attend": "md_attend.hip", "k_rows": "md_rows.hip", "k_logits": "md_kernels.hip"}
-HEADERS = ("md_internal.h", "md_device.h")   # included by both sources
+KERNEL_SOURCES = {"k_attend": ("md_attend.hip",), "k_rows": ("md_rows.hip", "md_arrive.h"),
+                  "k_logits": ("md_kernels.hip",)}
+HEADERS = ("md_internal.h", "md_device.h")   # included by every source
 
 
 def source_hash(kernel: str) -> str:
-    """Hash of the kernel's source file and the headers it includes: a
+    """Hash of the kernel's source files and the headers they include: a
     counter profile holds for the code it was taken on."""
     h = hashlib.sha256()
-    for name in (KERNEL_SOURCES[kernel],) + HEADERS:
+    for name in KERNEL_SOURCES[kernel] + HEADERS:
         with open(os.path.join(CSRC, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
