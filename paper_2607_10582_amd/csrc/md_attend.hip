@@ -226,6 +226,12 @@ __device__ __forceinline__ float half_row(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true));   // row_ror:8
 }
 
+// Row groups: the partial-mass word of a void step.  A mass that is a NaN of
+// its own (from a key that is not finite) goes out with other bits: only a
+// query that is not finite, or a time-out, voids a step.
+constexpr uint32_t kVoidMass = 0xffffffffu;
+__device__ __forceinline__ uint32_t mass_bits(float m) { return m != m ? 0x7fc00000u : __float_as_uint(m); }
+
 struct Unit {
     int s, j, nt_s, nu, us;
     uint64_t deadline;   // real-time tick after which the unit stops waiting
@@ -826,7 +832,10 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         if constexpr (PK) ls += half_row(ls);
         ls = rows_sum(ls);
         after_tiles(row);
-        if (g == 0 && h < kSlots) wm_wave[(size_t)(row % kRowBufs) * W * kSlots + h] = ms;
+        // (the maximum itself, not ms: a wave with no logit for a head then
+        // weighs 2^-inf = 0; as 0 it would weigh 2^(0 - M), infinite for a
+        // row whose maximum M lies below -128, and 0 times that is a NaN)
+        if (g == 0 && h < kSlots) wm_wave[(size_t)(row % kRowBufs) * W * kSlots + h] = mx;
         if (g == 0 && h < G) sm.wstat[((row & 1) * W + wv) * 16 + h] = make_float2(mx, ls);
         lds_sync();
     };
@@ -859,9 +868,9 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     }
 
     // ---- row groups: every group but the first hands its tokens' partial
-    // masses to the unit of group 0 (same tokens) as tagged words, a NaN
-    // payload marking a void step; that unit adds them in group order and
-    // finishes the tokens alone.
+    // masses to the unit of group 0 (same tokens) as tagged words, kVoidMass
+    // marking a void step; that unit adds them in group order and finishes
+    // the tokens alone.
     if (un.rg > 1) {
         const bool void_here = *sm.vflag != 0;
         unsigned long long* pbase = a.upart + (size_t)(un.ubase + un.j) * kT + wtok0 + lane;
@@ -870,7 +879,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
 #pragma unroll
             for (int k = 0; k < kTok; ++k)
                 __hip_atomic_store(pbase + un.grp * gstride + 64 * k,
-                                   tag_hi | (void_here ? 0x7fc00000u : __float_as_uint(acc[k])),
+                                   tag_hi | (void_here ? kVoidMass : mass_bits(acc[k])),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (void_here && threadIdx.x == 0) a.valid[un.s] = 0;
             return;
@@ -903,9 +912,8 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
 #pragma unroll
                 for (int k = 0; k < kTok; ++k) {
                     if (g2 < un.rg) {
-                        const float pv = __uint_as_float((uint32_t)pw[g2 - 1][k]);
-                        bad |= pv != pv;
-                        acc[k] += pv;
+                        bad |= (uint32_t)pw[g2 - 1][k] == kVoidMass;
+                        acc[k] += __uint_as_float((uint32_t)pw[g2 - 1][k]);
                     }
                 }
             if (bad) *sm.vflag = 1;

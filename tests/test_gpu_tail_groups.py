@@ -26,9 +26,13 @@ def _need_gpu():
     B.load_library()
 
 
-def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, quant=0.0, fused=True):
+def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, quant=0.0, fused=True, low=False,
+        nan_token=None):
     """Two steps over sessions of `tokens` tokens; the same inputs for every
-    setting of row_groups.  Budgets keep every token, so slots line up."""
+    setting of row_groups.  Budgets keep every token, so slots line up.
+    low: every logit of the first and of the last (layer, KV head) lies near
+    -150, which shifts their softmax rows and changes no weight.  nan_token:
+    the key of this token of every session holds a NaN in one row."""
     gen = torch.Generator(device="cuda").manual_seed(11)
     S = len(tokens)
     # runs of 40 tokens: with region-aligned pages every third page is half full
@@ -39,6 +43,10 @@ def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, qua
     at = 0
     for s, n in enumerate(tokens):
         keys = torch.randn((n, L, Hkv, 128), generator=gen, device="cuda").to(torch.bfloat16)
+        if low:
+            keys[:, 0, 0, 0] = keys[:, L - 1, Hkv - 1, 0] = 40.0
+        if nan_token is not None:
+            keys[nan_token, L - 1, Hkv - 1, 5] = float("nan")
         cache.load_session(s, keys, regions[s], ids[at:at + pages[s]], budget=2 * n, clock=n, region_aligned=aligned)
         at += pages[s]
     cache.set_free_pages(ids[at:])
@@ -50,6 +58,10 @@ def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, qua
     for k in range(steps):
         q = torch.randn((S, window, L, Hq, 128), generator=gen, device="cuda")
         nk = torch.randn((S, L, Hkv, 128), generator=gen, device="cuda").to(torch.bfloat16)
+        if low:
+            G = Hq // Hkv
+            q[:, :, 0, :G, 0] = q[:, :, L - 1, Hq - G:, 0] = -150.0 * 128 ** 0.5 / 40.0
+            nk[:, 0, 0, 0] = nk[:, L - 1, Hkv - 1, 0] = 40.0
         reg = torch.full((S,), 1 + k, dtype=torch.uint8, device="cuda")
         md.observe(k, q, nk, reg, abar_out=abar)
         md.score()
@@ -92,3 +104,45 @@ def test_last_pass_in_row_groups_agrees_with_every_row(label, tokens, L, Hq, Hkv
     total = float(a[0][0].sum())
     assert abs(total - len(tokens)) < 1e-3 * len(tokens)   # every session's masses add up to 1
     print(f"[{label}] {n} units on {ca['workgroups']} workgroups ok", flush=True)
+
+
+# A row whose maximum lies below -128 in base 2: chunks without a live token
+# (8,100 tokens leave the last unit's fourth wave one) or, under a window,
+# hidden from an older query (the appended token alone in its chunk) must
+# weigh nothing there, and neither spoil a token's mass nor void a step.
+# LOW: a logit of 150 * 1.44 = 216 in base 2 is a float32 sum of about 1,700
+# times 0.13; each of its (up to 12) MFMA accumulations rounds by at most half
+# an ulp of that, 2^-14 * 0.13 = 7.8e-6, on either path, which moves the weight
+# by 24 * 7.8e-6 * ln 2 = 1.3e-4 of itself at most.
+LOW = 1.3e-4
+
+
+@pytest.mark.parametrize("tokens,kw", [
+    ([8100] * 17, {}),
+    ([7000] * 17, {"aligned": True}),
+    ([8064] * 9, {"window": 2}),
+    ([8100] * 17, {"quant": 10.0}),
+])
+@pytest.mark.parametrize("row_groups", [True, False])
+def test_very_low_logits_weigh_as_any_others(tokens, kw, row_groups):
+    a, ca = run(tokens, 8, 12, 2, 16, row_groups, low=True, **kw)
+    b, cb = run(tokens, 8, 12, 2, 16, False, fused=False, low=True, **kw)
+    assert ca["first_fused"] and not ca["spill"] and not cb["first_fused"]
+    for step, (x, y) in enumerate(zip(a, b)):
+        for u, v in zip(x[:3], y[:3]):
+            assert not np.isnan(v).any() and np.array_equal(np.isfinite(u), np.isfinite(v)), (kw, step)
+            fin = np.isfinite(v)
+            np.testing.assert_allclose(u[fin], v[fin], rtol=LOW, atol=1e-30, err_msg=f"{kw} step {step}")
+        assert np.array_equal(x[3], y[3])
+    assert abs(float(a[0][0].sum()) - len(tokens)) < 1e-3 * len(tokens)
+
+
+def test_a_key_that_is_not_finite_voids_no_step():
+    # only a query that is not finite does: the token's own mass is a NaN,
+    # with row groups (one session's units are split) as without
+    a, _ = run([8100] * 17, 8, 12, 2, 16, True, steps=1, nan_token=3000)
+    b, _ = run([8100] * 17, 8, 12, 2, 16, False, steps=1, nan_token=3000)
+    for u, v in zip(a[0][:2], b[0][:2]):
+        assert np.isnan(v).sum() == 17 and np.array_equal(np.isnan(u), np.isnan(v))
+        fin = np.isfinite(v)
+        np.testing.assert_allclose(u[fin], v[fin], rtol=REL, atol=1e-30)
