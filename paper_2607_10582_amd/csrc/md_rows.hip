@@ -474,7 +474,9 @@ __device__ __forceinline__ bool rows_work(const Dims& dm, const View& v, const S
         ls += __shfl_xor(ls, 16);
         ls += __shfl_xor(ls, 32);
         fold_stat(run_m, run_l, mx, ls);
-        if (g == 0) wm[c * 16 + h] = ms;
+        // (the maximum itself: a chunk that this column does not see weighs
+        // 2^-inf = 0 in its row, not 2^(0 - M), which is infinite for M below -128)
+        if (g == 0) wm[c * 16 + h] = mx;
         if (c != nc - 1) return;
         // ---- the row is complete: the waves' statistics meet, every wave
         // turns its held values into softmax weights

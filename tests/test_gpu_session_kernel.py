@@ -135,3 +135,50 @@ def test_observation_without_append_and_empty_free_list():
     assert c.n_tokens.cpu().tolist() == [64, 41] and int(c.free_count[0]) == 0
     assert abs(float(abar[c.page_table[1, :3].long()].sum()) - 1.0) < 1e-4
     p.close()
+
+
+@pytest.mark.parametrize("n,quant,aligned", [(64, 0.0, False), (600, 0.0, False), (640, 0.0, True), (640, 10.0, False)])
+def test_window_with_very_low_logits(n, quant, aligned):
+    # Every logit of two (layer, KV head) near -150 (a shift of their softmax
+    # rows): a chunk whose tokens an older query does not see (the appended
+    # token alone in it, for n a multiple of 64) weighs nothing in its row.
+    from test_gpu_tail_groups import LOW, run as two_steps
+    kw = dict(window=2, quant=quant, aligned=aligned, low=True)
+    a, _ = two_steps([n, 200], 2, 8, 2, 16, True, fused=None, **kw)
+    b, _ = two_steps([n, 200], 2, 8, 2, 16, True, fused=False, **kw)
+    for x, y in zip(a, b):
+        for u, v in zip(x[:3], y[:3]):
+            assert not np.isnan(u).any() and not np.isnan(v).any()
+            fin = np.isfinite(v)
+            assert np.array_equal(np.isfinite(u), fin)
+            np.testing.assert_allclose(u[fin], v[fin], rtol=LOW, atol=1e-30)
+
+
+@pytest.mark.parametrize("S,aligned", [(600, False), (1024, True)])
+def test_more_sessions_than_threads_and_cus(S, aligned):
+    # the commit takes two sessions per thread beyond 512, and the
+    # workgroups (one per session) run in several rounds over the CUs
+    n0s = [17 + (7 * s) % 48 for s in range(S)]
+    w = C.with_overrides(C.get("small"), S=S, n0=None, n0_range=(1, 2), Hq=4, Hkv=1, steps=4, system_len=8,
+                         region_aligned=aligned, append_run=3)
+    p = Pair(w, n0s=n0s, budgets=[n - 1 - s % 9 for s, n in enumerate(n0s)], fused=None,
+             oracle_sessions=[0, 1, 299, 511, 512, 513, S - 2, S - 1], check_free_list=True)
+    run(p, 4, f"{S} sessions")
+
+
+def test_two_handles_of_different_capacity_step_in_turn():
+    # one instantiation, two sizes of its LDS: the smaller handle comes
+    # second, and neither depends on the order
+    w = C.with_overrides(C.get("small"), L=4, steps=4)
+    a = Pair(C.with_overrides(w, n0=900), fused=None, max_pages=256)   # room for 4,096 tokens
+    b = Pair(C.with_overrides(w, n0=300), fused=None)
+    for p in (a, b):
+        p.md.profile(("attend", "append"))
+    for _ in range(4):
+        a.step()
+        b.step()
+    for p in (a, b):
+        assert p.md.profile_read("attend")[1] == 4 and p.md.profile_read("append")[1] == 0
+        assert p.device_status() == 0
+        p.close()
+
