@@ -272,7 +272,9 @@ md_status md_init(const md_config* cfg, const md_region_params* rp,
  * fused kernel's statistics, 16 bytes per softmax row (L Hq W) and 256-token
  * unit of the pool, plus, when the multi-kernel path can run, the logits of
  * every pool slot (4 L Hq W bytes each); a configuration that needs more than
- * 128 MiB gets MD_E_TOO_LARGE.  The handle itself is one of 16 static slots
+ * 128 MiB gets MD_E_TOO_LARGE (what is only for speed gives way first: the
+ * session kernel, the split of a last pass, and with a window, region-aligned
+ * or quantised pages all row groups).  The handle itself is one of 16 static slots
  * (MD_E_TOO_LARGE when all are taken; md_destroy gives it back).
  * md_init_static clears the part of the array the handle uses (the array
  * keeps whatever the previous static handle left there).  Every static

@@ -375,6 +375,7 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     int rg_first = 1, rg_steady = 1;
     int rows_first = 0, rows_steady = 0;   // row ranges of the session kernel (0: not used)
     const bool automatic = !(cfg->flags & (MD_FLAG_FUSED | MD_FLAG_NO_FUSED));
+    int64_t first = 0, steady = 0;   // units of the first and of the later observes
     if (dm.fused || automatic) {
         int32_t hn[md::kMaxSessions], hbud[md::kMaxSessions];
         if (hipMemcpyAsync(hn, cv->n_tokens, dm.S * sizeof(int32_t), hipMemcpyDeviceToHost, hs) != hipSuccess ||
@@ -382,7 +383,6 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
                 hipSuccess ||
             hipStreamSynchronize(hs) != hipSuccess)
             return MD_E_HIP;
-        int64_t first = 0, steady = 0;
         int64_t tok_first = 0, tok_steady = 0, max_first = 0, max_steady = 0;   // tokens, all and of one session
         for (int s = 0; s < dm.S; ++s) {
             const int64_t n = hn[s] > 0 ? hn[s] : 0;
@@ -428,11 +428,14 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
             }
             if (dm.rows_rg == 0) dm.rows_nc = rows_first = rows_steady = 0;
         }
-        const int64_t cap_units = ((int64_t)dm.MP * dm.P + dm.T - 1) / dm.T;
-        const int64_t rg_allow = rows_ok && dm.LHkv >= 2 * md::kMinGroupRows
+    }
+    const int64_t cap_units = ((int64_t)dm.MP * dm.P + dm.T - 1) / dm.T;
+    const int base_units = dm.U_cap;
+    auto choose_paths = [&](bool groups) {
+        const int64_t rg_allow = groups && dm.LHkv >= 2 * md::kMinGroupRows
                                      ? std::min<int64_t>({md::kMaxRowGroups, dm.LHkv / md::kMinGroupRows,
-                                                              dm.n_wg / std::max<int64_t>(cap_units, 1)})
-                                         : 1;
+                                                          dm.n_wg / std::max<int64_t>(cap_units, 1)})
+                                     : 1;
         auto pick = [&](int64_t u) -> int {
             if (!dm.fused || u <= 0 || 2 * u >= dm.n_wg) return 1;
             return (int)std::max<int64_t>(1, std::min<int64_t>(rg_allow, dm.n_wg / u));
@@ -445,15 +448,17 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         // against 55.5 us per step on the multi-kernel path; 4 sessions, 72
         // units, 46.8 against 44.7 us).
         auto fills = [&](int64_t u, int rg) { return (rg > 1 ? 4 : 2) * u * rg >= dm.n_wg; };
+        fused_first = fused_steady = dm.fused;
         if (!(cfg->flags & MD_FLAG_FUSED)) {
             fused_first = dm.fused && fills(first, rg_first);
             fused_steady = dm.fused && fills(steady, rg_steady);
         }
         if (!fused_first) rg_first = 1;
         if (!fused_steady) rg_steady = 1;
-    }
-    dm.rg_max = std::max(rg_first, rg_steady);
-    if (dm.fused) dm.U_cap *= dm.rg_max;
+        dm.rg_max = std::max(rg_first, rg_steady);
+        dm.U_cap = dm.fused ? base_units * dm.rg_max : base_units;
+    };
+    choose_paths(rows_ok);
     auto runs_multi = [&] {
         return dm.spill || (!fused_first && rows_first == 0) || (!fused_steady && rows_steady == 0);
     };
@@ -462,19 +467,29 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     // Units of a last pass that fills little of the grid split too (at most
     // the grid's worth more of them), unless the static scratch, large enough
     // for the plain plan, cannot hold their statistics and partial masses
-    // (nor the session kernel's, which then gives way too).
+    // (nor the session kernel's, which then gives way too).  Region-aligned,
+    // quantised and window handles then do without row groups altogether: a
+    // configuration of theirs that fits on units of every row is not refused.
+    // (Plain handles of one query keep them: MD_FLAG_NO_ROW_GROUPS is theirs
+    // to set.)
     const int plain_units = dm.U_cap;
     dm.tail = rows_ok && dm.fused ? std::min(md::kMaxRowGroups, dm.LHkv / md::kMinTailRows) : 1;
     if (dm.tail > 1) dm.U_cap += dm.n_wg; else dm.tail = 1;
     size_t bytes = md::scratch_bytes(dm);
-    if (use_static && bytes > md::kStaticScratchBytes) {
+    const auto too_large = [&] { return use_static && bytes > md::kStaticScratchBytes + md::row_group_words(dm.S); };
+    if (too_large()) {
         dm.tail = 1;
         dm.U_cap = plain_units;
         dm.rows_nc = dm.rows_rg = rows_first = rows_steady = 0;
         dm.multi = runs_multi();
         bytes = md::scratch_bytes(dm);
     }
-    if (use_static && bytes > md::kStaticScratchBytes) return MD_E_TOO_LARGE;
+    if (too_large() && dm.rg_max > 1 && (dm.aligned || dm.quant || dm.W > 1)) {
+        choose_paths(false);
+        dm.multi = runs_multi();
+        bytes = md::scratch_bytes(dm);
+    }
+    if (too_large()) return MD_E_TOO_LARGE;
     md_handle_s* h = use_static ? take_static_handle() : new (std::nothrow) md_handle_s();
     if (h == nullptr) return use_static ? MD_E_TOO_LARGE : MD_E_NOMEM;
     if (!use_static) h->static_slot = -1;

@@ -156,8 +156,10 @@ void scratch_carve(const Dims& dm, void* base, Scratch* sc);
 // md_init_static: the library's scratch in a file-scope device array of this
 // size (one per device, held until the process ends) instead of an
 // allocation.  static_scratch gives its address on the current device,
-// looked up once per device.
+// looked up once per device.  The words that hold each session's row groups
+// come on top, so that they push no configuration over the limit.
 constexpr size_t kStaticScratchBytes = (size_t)128 << 20;
+constexpr size_t row_group_words(int sessions) { return ((size_t)(sessions + 1) * sizeof(int32_t) + 255) & ~(size_t)255; }
 hipError_t static_scratch(void** ptr);
 
 // Launchers; each returns the hipError_t of its launch.

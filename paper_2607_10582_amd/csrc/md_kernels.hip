@@ -31,7 +31,7 @@ namespace md {
 // allocate device memory.  Host code must not pass the array's name to a
 // kernel or a copy (it stands for the host-side shadow); static_scratch
 // hands out the device address instead.
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + row_group_words(kMaxSessions)];
 
 hipError_t static_scratch(void** ptr) {
     constexpr int kMaxDevices = 64;

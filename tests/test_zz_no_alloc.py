@@ -107,3 +107,47 @@ def test_static_handle_rejects_a_scratch_beyond_the_static_array():
     st, h = B.md_init_raw(cfg, rp, c.view(), torch.cuda.current_stream().cuda_stream, static=True)
     assert st == B.MD_OK and h is not None
     B.md_destroy(h)
+
+
+def init_static(S, n_tokens=0, **kw):
+    """md_init_static on a small cache that says it has n_phys_pages pages;
+    no step runs, so no page beyond the cache's eight is touched."""
+    L, Hq, Hkv, P = kw["n_layers"], kw["n_q_heads"], kw["n_kv_heads"], kw["page_size"]
+    c = PagedCache(L=L, Hq=Hq, Hkv=Hkv, d=128, P=P, S=S, max_pages=kw["max_pages"], n_phys=8, device="cuda")
+    c.n_tokens[:] = n_tokens
+    c.budget[:] = n_tokens
+    b = torch.ones((S, 7), dtype=torch.float32, device="cuda")
+    cfg = B.md_config(head_dim=128, max_sessions=S, n_regions=7, pinned_region_mask=1, rho=0.9, alpha=1.0,
+                      tau_scale=2.0, **kw)
+    rp = B.md_region_params(base_priority=b.data_ptr(), decay_rate=b.data_ptr())
+    st, h = B.md_init_raw(cfg, rp, c.view(), torch.cuda.current_stream().cuda_stream, static=True)
+    if h is None:
+        return st, None
+    out = B.md_kernel_config(h)
+    B.md_destroy(h)
+    return st, out
+
+
+@pytest.mark.parametrize("kw", [dict(flags=B.MD_FLAG_FUSED | B.MD_FLAG_REGION_ALIGNED, window=1),
+                                dict(flags=B.MD_FLAG_FUSED, window=1, quant_threshold=0.3),
+                                dict(flags=B.MD_FLAG_FUSED, window=2)])
+def test_row_groups_give_way_where_the_static_array_cannot_hold_them(kw):
+    # 1,048,576 slots, 512 softmax rows: the unit statistics take 34 MB, in
+    # eight row groups with their partial masses 340 MB
+    hq = 16 // kw["window"]
+    st, cfg = init_static(1, 100, n_layers=32, n_q_heads=hq, n_kv_heads=2, page_size=16, max_pages=8,
+                          n_phys_pages=65536, **kw)
+    assert st == B.MD_OK and cfg["first_fused"] and cfg["first_row_groups"] == 1
+    # with room for them the row groups stay
+    st, cfg = init_static(1, 100, n_layers=32, n_q_heads=hq, n_kv_heads=2, page_size=16, max_pages=8,
+                          n_phys_pages=8, **kw)
+    assert st == B.MD_OK and cfg["first_row_groups"] == 8
+
+
+def test_the_static_array_takes_the_same_largest_configuration():
+    # the logits of 2,095,244 pages of one row, 1,024 sessions' work lists
+    # beside them: 128 MiB to the byte without the words that hold each
+    # session's row groups, which have room of their own behind the array
+    kw = dict(n_layers=1, n_q_heads=1, n_kv_heads=1, page_size=16, max_pages=4, flags=B.MD_FLAG_NO_FUSED, window=1)
+    assert init_static(1024, n_phys_pages=2095244, **kw)[0] == B.MD_OK
+    assert init_static(1024, n_phys_pages=2095245, **kw)[0] == B.MD_E_TOO_LARGE
