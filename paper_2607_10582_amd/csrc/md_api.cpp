@@ -420,9 +420,9 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
             rows_steady = pays(tok_steady, max_steady) ? rg : 0;
             dm.rows_rg = std::max(rows_first, rows_steady);
             if (dm.rows_rg > 0 &&
+                // (the most any handle takes: handles of other sizes share the function)
                 hipFuncSetAttribute(md::rows_kernel(dm.G * dm.W, dm.quant, dm.W),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)md::rows_lds_bytes(dm.G * dm.W, dm.rows_nc, dm.W)) != hipSuccess) {
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)md::kRowsLds) != hipSuccess) {
                 (void)hipGetLastError();
                 dm.rows_rg = 0;
             }
