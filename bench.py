@@ -14,8 +14,7 @@ The default workload is the ragged batch: 64 agent sessions of U[2,048,
 The same run also measures the ragged batch with 64-token pages, the
 long-horizon batch (16 sessions x 32,768 tokens, 1.5B shape, 25 % budget,
 128 steps) and the batch of short sessions (32 x 1,700 tokens, 3B shape,
-30 % budget, 256 steps, on the fused kernel with row groups) as
-sub-records.
+30 % budget, 256 steps, on the session kernel) as sub-records.
 
 For every workload, step 1 runs three times on a copy of the state first
 (so the code objects are loaded), then one trajectory from the fresh cache:
@@ -31,9 +30,9 @@ Printed on stdout: one JSON line.  value = tokens scored per second over the
 timed steps (the sum over sessions and timed steps of the cached tokens
 scored, divided by the wall time of the timed steps, bracketed by
 synchronisations); roofline = the dominant kernel's (the fused
-attention-mass kernel, or the attention-logits kernel of the multi-kernel
-path) algorithmic bytes per launch over its event-timed average duration,
-against MI355X's 8 TB/s; cpu_baseline = the CPU oracle, session-parallel on
+attention-mass kernel, the session kernel, or the attention-logits kernel of
+the multi-kernel path) algorithmic bytes per launch over its event-timed
+average duration, against MI355X's 8 TB/s; cpu_baseline = the CPU oracle, session-parallel on
 the host's cores, on a sample of the same workload.
 """
 from __future__ import annotations
@@ -272,27 +271,21 @@ def measure(w, W: int, K: int, dev, *, multi_kernel=False, calibrate=0, offload_
     # eviction) are counted on their own
     c_start = md.counters()
     first_end = torch.cuda.Event(enable_timing=True)
-    appends = 1
     for k in range(1, W + 1):
         ev[k - 1].record(stream)
-        if k > 1 and inputs[k - 1][0] is not None:
-            md.profile(("append",))
         run(k)
         if k == 1:
             first_end.record(stream)
             c_first = md.counters()
-        elif inputs[k - 1][0] is not None:
-            appends = md.profile_read("append")[1]
-            md.profile(())
     ev[W].record(stream)
     torch.cuda.synchronize(dev)
     c0 = md.counters()
-    kcfg = md.kernel_config()
-    # the session kernel appends in its own launch (and is timed as "attend")
-    session = appends == 0
+    kcfg, path = md.kernel_config(), md.observe_path()
+    # the session kernel appends in its own launch, and is timed as "attend"
+    session = path["steady"] == "session"
     hot = "attend" if session or (kcfg["steady_fused"] and not kcfg["spill"]) else "logits"
     hot_kernel = "rows" if session else hot
-    log(f"kernel config {kcfg}; timing k_{hot_kernel}")
+    log(f"kernel config {kcfg}, path {path}; timing k_{hot_kernel}")
     md.profile((hot,))
     q_tok0 = quantised_tokens(cache) if w.quant_threshold > 0 else 0
     if calibrate:
@@ -353,8 +346,8 @@ def measure(w, W: int, K: int, dev, *, multi_kernel=False, calibrate=0, offload_
     n_obs = sum(1 for k in range(W + 1, W + K + 1) if g.observes(w, k))
     q_bytes = w.S * w.L * w.Hq * w.d * 4 * w.window * n_obs / K
     # algorithmic bytes over the timed launches: every cached key once and the
-    # queries once; the fused kernel also reads and writes each token's
-    # importance (Eq. 2), reads its refresh clock and region (Eq. 3, Eq. 4),
+    # queries once; the fused and the session kernel also read and write each
+    # token's importance (Eq. 2), reads its refresh clock and region (Eq. 3, Eq. 4),
     # and reads each page's table entry and writes its score (Eq. 5)
     if hot == "attend":
         hot_bytes = scored * (kb + 13) + (scored // w.P) * 8 + K * q_bytes - q_saved
@@ -402,10 +395,8 @@ def measure(w, W: int, K: int, dev, *, multi_kernel=False, calibrate=0, offload_
                                      if calibrate and cal_ev else None),
         "step_algorithmic_gbs": step_bytes / wall / 1e9,
         "step_frac_of_peak": step_bytes / wall / 1e9 / PEAK_HBM_GBS,
-        "observe_path": {"first": "fused" if kcfg["first_fused"] else "multi-kernel",
-                         "first_row_groups": kcfg["first_row_groups"],
-                         "steady": "session" if session else "fused" if kcfg["steady_fused"] else "multi-kernel",
-                         "steady_row_groups": kcfg["steady_row_groups"]},
+        "observe_path": {"first": path["first"], "first_row_groups": path["first_ranges"],
+                         "steady": path["steady"], "steady_row_groups": path["steady_ranges"]},
     }
     if offload_pages > 0:
         # offload tier: pages moved over the host link in the timed steps,

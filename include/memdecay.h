@@ -454,12 +454,27 @@ md_status md_read_counters(md_handle h, int64_t* out);
  * fused kernel's workgroups (all resident at once), out[4] 1 when the first
  * md_observe_step runs the fused kernel, out[5] 1 when the later ones do,
  * out[6] and out[7] the row groups of their fused units (1: none; see
- * MD_FLAG_NO_ROW_GROUPS).  With neither MD_FLAG_FUSED nor MD_FLAG_NO_FUSED a
- * batch of short sessions takes the session kernel instead of the path that
- * out[4] or out[5] names (timed as MD_K_ATTEND; it appends in the same
- * launch, so MD_K_APPEND then times only steps without an observation).
- * Host-only, no device work. */
+ * MD_FLAG_NO_ROW_GROUPS).  Host-only, no device work. */
 md_status md_kernel_config(md_handle h, int32_t* out);
+
+/* Paths of an observation (md_observe_path). */
+enum {
+    MD_PATH_MULTI = 0,    /* the multi-kernel path (logits through HBM)          */
+    MD_PATH_FUSED = 1,    /* the fused kernel                                    */
+    MD_PATH_SESSION = 2   /* the session kernel (short sessions, with neither    */
+                          /* MD_FLAG_FUSED nor MD_FLAG_NO_FUSED): append and     */
+                          /* observation in one launch, timed as MD_K_ATTEND, so */
+                          /* that MD_K_APPEND times only steps without an        */
+                          /* observation                                         */
+};
+
+/* Which path the observations run on (out: 4 ints): out[0] the first
+ * md_observe_step's MD_PATH_*, out[1] the later ones', out[2] and out[3] into
+ * how many ranges of the L Hkv rows they split each session (the session
+ * kernel, a workgroup each) or each fused unit (its row groups; a step's last
+ * pass may take more); 1 on the multi-kernel path.  Host-only, no device
+ * work. */
+md_status md_observe_path(md_handle h, int32_t* out);
 
 /*
  * md_calib_accumulate — region-lifetime statistics for the calibration of

@@ -37,9 +37,13 @@ MD_REGION_HOLE = 0xFF
 
 EXPORTS = ("md_abi_version", "md_status_str", "md_init", "md_init_static", "md_observe_step",
            "md_score_pages", "md_select_evict", "md_compact", "md_select_compact", "md_read_device_status",
-           "md_profile_enable", "md_profile_read", "md_read_counters", "md_kernel_config",
+           "md_profile_enable", "md_profile_read", "md_read_counters", "md_kernel_config", "md_observe_path",
            "md_calib_accumulate", "md_calib_fit",
            "md_destroy")
+
+# paths of md_observe_path
+PATHS = ("multi-kernel", "fused", "session")
+MD_PATH_MULTI, MD_PATH_FUSED, MD_PATH_SESSION = range(3)
 
 # kernel ids of md_profile_enable / md_profile_read
 KERNELS = ("append", "logits", "rowstats", "mass", "score", "select", "compact", "attend", "evict")
@@ -149,6 +153,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.md_calib_fit.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp]
     lib.md_kernel_config.restype = i32
     lib.md_kernel_config.argtypes = [vp, ctypes.POINTER(i32)]
+    lib.md_observe_path.restype = i32
+    lib.md_observe_path.argtypes = [vp, ctypes.POINTER(i32)]
     lib.md_destroy.restype = i32
     lib.md_destroy.argtypes = [vp]
     _lib = lib
@@ -278,6 +284,15 @@ def md_kernel_config(h: int) -> dict:
     return {"fused": bool(out[0]), "spill": bool(out[1]), "unit_max": int(out[2]), "workgroups": int(out[3]),
             "first_fused": bool(out[4]), "steady_fused": bool(out[5]), "first_row_groups": int(out[6]),
             "steady_row_groups": int(out[7])}
+
+
+def md_observe_path(h: int) -> dict:
+    """The path of the first and of the later observations (PATHS), and the
+    row ranges or groups of each."""
+    out = (ctypes.c_int32 * 4)()
+    _check("md_observe_path", load_library().md_observe_path(h, out))
+    return {"first": PATHS[out[0]], "steady": PATHS[out[1]], "first_ranges": int(out[2]),
+            "steady_ranges": int(out[3])}
 
 
 def md_destroy(h: int) -> int:

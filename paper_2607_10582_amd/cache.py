@@ -281,6 +281,9 @@ class MemDecay:
     def kernel_config(self) -> dict:
         return B.md_kernel_config(self.handle)
 
+    def observe_path(self) -> dict:
+        return B.md_observe_path(self.handle)
+
     def close(self):
         if self.handle is not None:
             B.md_destroy(self.handle)

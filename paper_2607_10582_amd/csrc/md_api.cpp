@@ -850,10 +850,20 @@ md_status md_kernel_config(md_handle h, int32_t* out) {
     out[1] = h->dm.spill;
     out[2] = h->dm.fused ? h->dm.T : 0;
     out[3] = h->dm.n_wg;
-    out[4] = h->fused_first ? 1 : 0;
-    out[5] = h->fused_steady ? 1 : 0;
-    out[6] = h->rg_first;
-    out[7] = h->rg_steady;
+    out[4] = h->rows_first == 0 && h->fused_first ? 1 : 0;
+    out[5] = h->rows_steady == 0 && h->fused_steady ? 1 : 0;
+    out[6] = out[4] ? h->rg_first : 1;
+    out[7] = out[5] ? h->rg_steady : 1;
+    return MD_OK;
+}
+
+md_status md_observe_path(md_handle h, int32_t* out) {
+    if (h == nullptr || out == nullptr) return MD_E_INVALID;
+    auto path = [](int rows, bool fused) { return rows > 0 ? MD_PATH_SESSION : fused ? MD_PATH_FUSED : MD_PATH_MULTI; };
+    out[0] = path(h->rows_first, h->fused_first);
+    out[1] = path(h->rows_steady, h->fused_steady);
+    out[2] = h->rows_first > 0 ? h->rows_first : h->rg_first;
+    out[3] = h->rows_steady > 0 ? h->rows_steady : h->rg_steady;
     return MD_OK;
 }
 

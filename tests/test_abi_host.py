@@ -186,6 +186,7 @@ def test_calls_reject_a_null_handle(lib):
     assert L.md_destroy(None) == B.MD_E_INVALID
     out = ctypes.c_int32()
     assert L.md_read_device_status(None, ctypes.byref(out)) == B.MD_E_INVALID
+    assert L.md_observe_path(None, ctypes.byref(out)) == B.MD_E_INVALID
     assert L.md_init(None, None, None, None, None) == B.MD_E_INVALID
 
 

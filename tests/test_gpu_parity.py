@@ -265,19 +265,30 @@ def test_selection_on_scores_of_the_fused_kernel():
         assert np.array_equal(x, y)
 
 
-@pytest.mark.parametrize("name,steady_fused", [("qwen15_1700", False), ("long32k", True), ("qwen3_32x1700", True)])
-def test_library_picks_the_path(name, steady_fused):
-    # Without a path flag the library runs the multi-kernel path for small
-    # caches and the fused kernel for large ones (for a batch of small ones
-    # with row groups); either way the steps match the oracle.
+@pytest.mark.parametrize("name,steady,max_pages", [
+    ("qwen15_1700", "session", None), ("qwen3_32x1700", "session", None), ("long32k", "fused", None),
+    # page tables with room for more than a session's rows in LDS
+    ("qwen15_1700", "multi-kernel", 257), ("qwen3_32x1700", "fused", 257)])
+def test_library_picks_the_path(name, steady, max_pages):
+    # Without a path flag the library runs short sessions on the session
+    # kernel; where that cannot hold them, small caches on the multi-kernel
+    # path and large ones on the fused kernel (a batch of small ones with row
+    # groups).  Either way the steps match the oracle, and the path that is
+    # reported is the one that launches.
     w = C.get(name)
     big = w.name == "long32k"
-    p = Pair(w, fused=None, backend="torch" if big else "numpy",
+    p = Pair(w, fused=None, backend="torch" if big else "numpy", max_pages=max_pages,
              oracle_sessions=[3] if big else None, steps=4 if big else 12)
-    cfg = p.md.kernel_config()
-    say(f"[{name}] kernel config {cfg}")
-    assert cfg["steady_fused"] == steady_fused
-    run_pair(p, 3 if big else 12, f"{name}-auto")
+    cfg, path = p.md.kernel_config(), p.md.observe_path()
+    say(f"[{name}] kernel config {cfg}, path {path}")
+    assert path["steady"] == steady and cfg["steady_fused"] == (steady == "fused")
+    p.step()
+    p.md.profile(("attend", "append", "logits"))
+    p.step()
+    n = tuple(p.md.profile_read(k)[1] for k in ("attend", "append", "logits"))
+    p.md.profile(())
+    assert n == {"session": (1, 0, 0), "fused": (1, 1, 0), "multi-kernel": (0, 1, 1)}[steady]
+    run_pair(p, 1 if big else 10, f"{name}-auto")
 
 
 @pytest.mark.parametrize("fused", [True, False])

@@ -55,22 +55,24 @@ def test_library_splits_rows_for_a_small_batch():
     # fused kernel with two row groups for the first and eight (of nine rows)
     # for the later ones.  With 8 sessions (16 units, 144 with nine groups)
     # row groups still fill a quarter of the grid and take both; with 4 (8
-    # units, 72) the later observes take the multi-kernel path.
+    # units, 72) the later observes take the multi-kernel path.  (Page tables
+    # of 257 pages: the session kernel holds no more than 4,096 tokens.)
     w = C.with_overrides(C.get("qwen3_32x1700"), steps=16)
-    p = Pair(w, fused=None, select_compact=True, oracle_sessions=[0, 13, 31])
+    p = Pair(w, fused=None, select_compact=True, oracle_sessions=[0, 13, 31], max_pages=257)
     cfg = p.md.kernel_config()
     assert cfg["first_fused"] and cfg["steady_fused"]
     assert cfg["first_row_groups"] == 2 and cfg["steady_row_groups"] == 8
     st = run_pair(p, 16, "rows-auto-qwen3-32")
     assert st.evicted_pages > 3 * 60
-    p8 = Pair(C.with_overrides(w, S=8), fused=None, oracle_sessions=[0, 7])
+    p8 = Pair(C.with_overrides(w, S=8), fused=None, oracle_sessions=[0, 7], max_pages=257)
     cfg8 = p8.md.kernel_config()
     assert cfg8["first_fused"] and cfg8["first_row_groups"] == 9
     assert cfg8["steady_fused"] and cfg8["steady_row_groups"] == 9
     run_pair(p8, 16, "rows-auto-qwen3-8")
-    p4 = Pair(C.with_overrides(w, S=4), fused=None, oracle_sessions=[])
+    p4 = Pair(C.with_overrides(w, S=4), fused=None, oracle_sessions=[], max_pages=257)
     cfg4 = p4.md.kernel_config()
     assert cfg4["first_fused"] and not cfg4["steady_fused"]
+    assert p4.md.observe_path()["steady"] == "multi-kernel"
     p4.close()
 
 

@@ -87,7 +87,7 @@ def test_offload_tier():
     w = C.with_overrides(C.get("small"), L=2, S=3, n0=None, n0_range=(1, 2), steps=40, system_len=60)
     p = Pair(w, n0s=[450, 700, 300], budgets=[225, 300, 200], planted=24, planted_strength=2.5, query_gain=0.7,
              fused=None, offload_pages=8, drop_threshold=1e-3)
-    assert not p.md.kernel_config()["steady_fused"]
+    assert p.md.observe_path()["first"] == p.md.observe_path()["steady"] == "session"
     st = run_offload(p, 40, "session-offload")
     assert st.offloaded > 20 and st.recalled > 10
 

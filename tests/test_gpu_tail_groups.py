@@ -95,6 +95,9 @@ def test_last_pass_in_row_groups_agrees_with_every_row(label, tokens, L, Hq, Hkv
     assert ca["first_fused"] and not ca["spill"] and ca["first_row_groups"] == cb["first_row_groups"] == 1
     n = ca["units"]
     assert n > ca["workgroups"] or label == "one-pass"
+    # the groups' sums round differently, so masses that are the same to the
+    # bit come from the same plan: only the one-pass batch is split neither way
+    assert np.array_equal(a[0][0], b[0][0]) == (label == "one-pass")
     for step, (x, y) in enumerate(zip(a, b)):
         for u, v in zip(x[:3], y[:3]):
             assert np.array_equal(np.isfinite(u), np.isfinite(v))
