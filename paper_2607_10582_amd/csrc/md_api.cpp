@@ -376,6 +376,7 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     int rows_first = 0, rows_steady = 0;   // row ranges of the session kernel (0: not used)
     const bool automatic = !(cfg->flags & (MD_FLAG_FUSED | MD_FLAG_NO_FUSED));
     int64_t first = 0, steady = 0;   // units of the first and of the later observes
+    int64_t tok_first = 0, tok_steady = 0, max_first = 0, max_steady = 0;   // tokens, all and of one session
     if (dm.fused || automatic) {
         int32_t hn[md::kMaxSessions], hbud[md::kMaxSessions];
         if (hipMemcpyAsync(hn, cv->n_tokens, dm.S * sizeof(int32_t), hipMemcpyDeviceToHost, hs) != hipSuccess ||
@@ -383,7 +384,6 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
                 hipSuccess ||
             hipStreamSynchronize(hs) != hipSuccess)
             return MD_E_HIP;
-        int64_t tok_first = 0, tok_steady = 0, max_first = 0, max_steady = 0;   // tokens, all and of one session
         for (int s = 0; s < dm.S; ++s) {
             const int64_t n = hn[s] > 0 ? hn[s] : 0;
             const int64_t b = hbud[s] >= 0 ? (int64_t)hbud[s] + 1 : n;
@@ -446,12 +446,21 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         // units walk few rows, from a quarter (measured on batches of
         // 1,700-token sessions: 8 sessions, 144 units of nine groups, 49.5
         // against 55.5 us per step on the multi-kernel path; 4 sessions, 72
-        // units, 46.8 against 44.7 us).
-        auto fills = [&](int64_t u, int rg) { return (rg > 1 ? 4 : 2) * u * rg >= dm.n_wg; };
+        // units, 46.8 against 44.7 us).  Their tokens count too, each once
+        // per group: a unit takes as long with few, so they have to be an
+        // even share of 100 per CU for every row that a unit walks, or of 130
+        // where more than eight columns leave a CU one workgroup (with fewer,
+        // fused against multi-kernel path: 16 sessions of 510 tokens under a
+        // window of two queries, 16 columns, 60 against 48 us, 32 of them 63
+        // against 60; 96 of 105, 28 rows of 16 columns, 86 against 67).
+        const int64_t share = dm.G * dm.W > 8 ? 130 : 100;
+        auto fills = [&](int64_t u, int64_t tokens, int rg) {
+            return rg > 1 ? 4 * u * rg >= dm.n_wg && tokens * rg >= share * n_cu : 2 * u >= dm.n_wg;
+        };
         fused_first = fused_steady = dm.fused;
         if (!(cfg->flags & MD_FLAG_FUSED)) {
-            fused_first = dm.fused && fills(first, rg_first);
-            fused_steady = dm.fused && fills(steady, rg_steady);
+            fused_first = dm.fused && fills(first, tok_first, rg_first);
+            fused_steady = dm.fused && fills(steady, tok_steady, rg_steady);
         }
         if (!fused_first) rg_first = 1;
         if (!fused_steady) rg_steady = 1;

@@ -76,6 +76,18 @@ def test_library_splits_rows_for_a_small_batch():
     p4.close()
 
 
+@pytest.mark.parametrize("S,steady", [(16, "multi-kernel"), (32, "multi-kernel"), (48, "fused")])
+def test_row_groups_need_tokens_to_walk_for(S, steady):
+    # 16 rows of 16 columns (eight heads, two window queries) in two groups:
+    # 500 tokens a session fill a quarter of the grid with 16 sessions, but
+    # the fused kernel pays off only from about 130 tokens per CU and group
+    w = C.with_overrides(C.get("small"), L=8, Hq=16, Hkv=2, S=S, window=2, obs_interval=2, n0=None, n0_range=(1, 2),
+                         steps=4)
+    p = Pair(w, n0s=[505] * S, budgets=[499] * S, oracle_sessions=[0, S - 1], fused=None, max_pages=257)
+    assert p.md.observe_path()["steady"] == steady
+    run_pair(p, 4, f"window-rows-{S}")
+
+
 @pytest.mark.parametrize("L,Hq,Hkv,groups", [(13, 16, 2, 3), (8, 16, 2, 2), (28, 8, 1, 3), (36, 16, 2, 9)])
 def test_row_groups_even_and_uneven_splits(L, Hq, Hkv, groups):
     # L * Hkv rows in `groups` ranges of floor / ceil (L * Hkv / groups) rows:
