@@ -395,39 +395,6 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
             max_first = std::max(max_first, n);
             max_steady = std::max(max_steady, k);
         }
-        // Session kernel: short sessions whose rows all fit its LDS (whatever
-        // they grow to, so by the page table's capacity).  Each session takes
-        // as many row ranges as give every CU a workgroup, of equal numbers of
-        // rows.  It is picked when no workgroup has much more to read than an
-        // even share over the CUs: it saves the append's launch and the rows'
-        // exchange or the logits' way through memory, about 16 us, the time
-        // of 1,560 tokens of one row on one CU (25 GB/s of the full chip's
-        // rate).  Measured per step, sessions of 1,700 tokens at 30-40 %
-        // budget: 1 (1.5B shape) 28 against 37 us on the multi-kernel path, 4
-        // 32 against 46, 16 53 against 68 on the fused kernel, 32 80 against
-        // 85; 24 of 1,000-1,700 tokens at 50 % (uneven: the longest has 27 %
-        // more than the mean) 92 against 88, left to the fused kernel.
-        dm.rows_nc = automatic ? md::rows_chunks(dm.G * dm.W, dm.W, (int64_t)dm.MP * dm.P) : 0;
-        if (dm.rows_nc > 0) {
-            const int most = std::max(1, std::min(n_cu / dm.S, md::kMaxRowRanges));
-            const int rows = (dm.LHkv + most - 1) / most;   // rows per workgroup
-            const int rg = (dm.LHkv + rows - 1) / rows;
-            const int64_t rounds = ((int64_t)dm.S * rg + n_cu - 1) / n_cu;
-            auto pays = [&](int64_t tokens, int64_t longest) {
-                return longest * rows * rounds < tokens * dm.LHkv / n_cu + 1560;
-            };
-            rows_first = pays(tok_first, max_first) ? rg : 0;
-            rows_steady = pays(tok_steady, max_steady) ? rg : 0;
-            dm.rows_rg = std::max(rows_first, rows_steady);
-            if (dm.rows_rg > 0 &&
-                // (the most any handle takes: handles of other sizes share the function)
-                hipFuncSetAttribute(md::rows_kernel(dm.G * dm.W, dm.quant, dm.W),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)md::kRowsLds) != hipSuccess) {
-                (void)hipGetLastError();
-                dm.rows_rg = 0;
-            }
-            if (dm.rows_rg == 0) dm.rows_nc = rows_first = rows_steady = 0;
-        }
     }
     const int64_t cap_units = ((int64_t)dm.MP * dm.P + dm.T - 1) / dm.T;
     const int base_units = dm.U_cap;
@@ -468,6 +435,52 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         dm.U_cap = dm.fused ? base_units * dm.rg_max : base_units;
     };
     choose_paths(rows_ok);
+
+    // Session kernel: short sessions whose rows all fit its LDS (whatever
+    // they grow to, so by the page table's capacity).  Each session takes as
+    // many row ranges as give every CU a workgroup, of equal numbers of rows.
+    // It is picked when the workgroup with most to read is done before the
+    // other path would be.  In tokens of one row on one CU, about 9 ns each
+    // (28 GB/s): a row costs its session's tokens and 200 more (its barrier
+    // and statistics; 300 under a window), and each 512 tokens of the session 400 and 5 per range
+    // at the end (the tokens' state and the ranges' partial masses, on one
+    // CU).  The others' launches, exchange of rows or logits' way through
+    // memory take some 3,300 (30 us) more than that whatever the size; then
+    // the fused kernel an even share of the keys at three quarters of that
+    // rate, or 200 for each row its units walk (500 above eight columns,
+    // where a CU holds one workgroup), the multi-kernel path the share at
+    // half the rate.  Fitted to the times of both sides over 2,649 batches
+    // (1-256 sessions of 100-3,300 tokens, equal and uneven, 4-256 rows,
+    // every layout and tier): of the 2,110 it picks 133 are more than 3 %
+    // slower than the other path (at worst 17 %), of the others 41 would be
+    // faster.  Per step, sessions of 1,700 tokens at 30-40 % budget: 1 (1.5B
+    // shape) 25 against 35 us, 4 31 against 41, 32 (3B) 77 against 84; 2 of
+    // 2,700 tokens (3B) 59 against 44, 96 of 105 tokens 123 against 89, left
+    // to the fused kernel.
+    dm.rows_nc = automatic ? md::rows_chunks(dm.G * dm.W, dm.W, (int64_t)dm.MP * dm.P) : 0;
+    if (dm.rows_nc > 0) {
+        const int64_t most = std::max(1, std::min(n_cu / dm.S, md::kMaxRowRanges));
+        const int64_t rows = (dm.LHkv + most - 1) / most;   // rows per workgroup
+        const int64_t rg = (dm.LHkv + rows - 1) / rows;
+        const int64_t rounds = ((int64_t)dm.S * rg + n_cu - 1) / n_cu;
+        auto pays = [&](int64_t tokens, int64_t longest, bool fused, int groups) {
+            const int64_t own = rows * rounds * ((dm.W > 1 ? 300 : 200) + longest) + (400 + 5 * rg) * ((longest + 511) / 512);
+            const int64_t share = tokens * dm.LHkv / n_cu;
+            const int64_t walk = (dm.G * dm.W > 8 ? 500 : 200) * (int64_t)((dm.LHkv + groups - 1) / groups);
+            return own < (fused ? 3200 + std::max(share * 13 / 10, walk) : 3400 + 2 * share);
+        };
+        rows_first = pays(tok_first, max_first, fused_first, rg_first) ? (int)rg : 0;
+        rows_steady = pays(tok_steady, max_steady, fused_steady, rg_steady) ? (int)rg : 0;
+        dm.rows_rg = std::max(rows_first, rows_steady);
+        // (the most any handle takes: handles of other sizes share the function)
+        if (dm.rows_rg > 0 &&
+            hipFuncSetAttribute(md::rows_kernel(dm.G * dm.W, dm.quant, dm.W),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)md::kRowsLds) != hipSuccess) {
+            (void)hipGetLastError();
+            dm.rows_rg = 0;
+        }
+        if (dm.rows_rg == 0) dm.rows_nc = rows_first = rows_steady = 0;
+    }
     auto runs_multi = [&] {
         return dm.spill || (!fused_first && rows_first == 0) || (!fused_steady && rows_steady == 0);
     };

@@ -62,9 +62,12 @@ def test_session_sizes(P, aligned):
 
 @pytest.mark.parametrize("one_call", [False, True])
 def test_large_sessions(one_call):
-    # several chunks a wave: 2,100 and 2,900 tokens beside a short session
-    w = C.with_overrides(C.get("small"), L=36, Hq=8, Hkv=2, S=3, n0=None, n0_range=(1, 2), steps=5, system_len=100)
-    run(Pair(w, n0s=[2900, 2100, 70], budgets=[1700, 2000, 70], fused=None, select_compact=one_call), 5, "large")
+    # several chunks a wave: a batch of 2,900 and 2,100 tokens beside a short
+    # session (alone, sessions as long take the other paths)
+    n0s = [2900] * 30 + [2100, 70]
+    w = C.with_overrides(C.get("small"), L=4, Hq=8, Hkv=2, S=32, n0=None, n0_range=(1, 2), steps=5, system_len=100)
+    run(Pair(w, n0s=n0s, budgets=[2700] * 30 + [2000, 70], fused=None, select_compact=one_call,
+             oracle_sessions=[0, 17, 30, 31]), 5, "large")
 
 
 @pytest.mark.parametrize("aligned", [False, True])
@@ -182,3 +185,20 @@ def test_two_handles_of_different_capacity_step_in_turn():
         assert p.device_status() == 0
         p.close()
 
+
+
+@pytest.mark.parametrize("S,n0,window,steady", [
+    (1, 1500, 1, "session"), (2, 2800, 1, "fused"), (12, 1600, 1, "session"), (96, 105, 1, "fused"),
+    (96, 105, 2, "fused"), (4, 500, 2, "session")])
+def test_the_session_kernel_is_picked_where_it_is_the_faster_one(S, n0, window, steady):
+    # 72 rows (3B shape; half the heads under a window): not for a few long
+    # sessions, whose ends one CU adds up, nor for many of a few tokens, each
+    # of whose rows has its fixed cost
+    w = C.with_overrides(C.get("small"), L=36, Hq=16 // window, Hkv=2, S=S, n0=None, n0_range=(1, 2), window=window,
+                         obs_interval=window, steps=2, system_len=8)
+    p = Pair(w, n0s=[n0] * S, budgets=[n0 - 1] * S, oracle_sessions=[0], fused=None, max_pages=200)
+    assert p.md.observe_path()["steady"] == steady
+    for _ in range(2):
+        p.step()
+    assert p.device_status() == 0
+    p.close()
