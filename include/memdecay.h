@@ -148,10 +148,11 @@ enum {
                                 /* and of the later ones from the cache's sizes */
                                 /* and budgets at init: the session kernel (a   */
                                 /* workgroup per session and range of rows) for */
-                                /* short sessions; else the fused kernel, which */
-                                /* walks the layers in order, or for small      */
-                                /* caches the multi-kernel path, parallel over  */
-                                /* layers                                       */
+                                /* short sessions, until appends have made them */
+                                /* too long for it (empty ones count as full);  */
+                                /* else the fused kernel, which walks the       */
+                                /* layers in order, or for small caches the     */
+                                /* multi-kernel path, parallel over layers      */
 #define MD_FLAG_NO_ROW_GROUPS 0x20 /* keep every fused unit on all L Hkv rows. */
                                 /* By default a step whose units would fill     */
                                 /* less than half of the fused kernel's grid    */
@@ -472,8 +473,9 @@ enum {
  * md_observe_step's MD_PATH_*, out[1] the later ones', out[2] and out[3] into
  * how many ranges of the L Hkv rows they split each session (the session
  * kernel, a workgroup each) or each fused unit (its row groups; a step's last
- * pass may take more); 1 on the multi-kernel path.  Host-only, no device
- * work. */
+ * pass may take more); 1 on the multi-kernel path.  Sessions that outgrow
+ * the session kernel as tokens are appended leave it, and out[1] and out[3]
+ * then name the path from here on.  Host-only, no device work. */
 md_status md_observe_path(md_handle h, int32_t* out);
 
 /*

@@ -44,6 +44,8 @@ struct md_handle_s {
     int rg_steady;       // and on later ones (1: every unit walks every row)
     int rows_first;      // row ranges of the session kernel on the first observe
     int rows_steady;     // and on later ones (0: the paths above)
+    int64_t rows_limit;  // appends up to which the later ones take the session kernel
+    int64_t appended;    // appends enqueued (md_observe_step calls with keys)
     int64_t observed;    // observes enqueued
     Phase phase;
     const int32_t* sel_serial;   // md_select_evict's lists since the last observe
@@ -132,6 +134,12 @@ hipError_t timed_launch(md_handle_s* h, int id, F&& fn) {
 uint32_t next_word_tag(md_handle_s* h) {
     h->word_tag = (h->word_tag % md::kWordTagMask) + 1;
     return h->word_tag;
+}
+
+// Row ranges of the session kernel at the next observe (0: the other paths).
+int rows_now(const md_handle_s* h, bool first) {
+    if (first) return h->rows_first;
+    return h->appended <= h->rows_limit ? h->rows_steady : 0;
 }
 
 void release_events(md_handle_s* h) {
@@ -374,11 +382,12 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     bool fused_first = dm.fused, fused_steady = dm.fused;
     int rg_first = 1, rg_steady = 1;
     int rows_first = 0, rows_steady = 0;   // row ranges of the session kernel (0: not used)
+    int64_t rows_limit = INT64_MAX;        // appends up to which later observes use it
     const bool automatic = !(cfg->flags & (MD_FLAG_FUSED | MD_FLAG_NO_FUSED));
     int64_t first = 0, steady = 0;   // units of the first and of the later observes
-    int64_t tok_first = 0, tok_steady = 0, max_first = 0, max_steady = 0;   // tokens, all and of one session
+    int64_t tok_first = 0, tok_steady = 0;   // and tokens
+    int32_t hn[md::kMaxSessions], hbud[md::kMaxSessions];
     if (dm.fused || automatic) {
-        int32_t hn[md::kMaxSessions], hbud[md::kMaxSessions];
         if (hipMemcpyAsync(hn, cv->n_tokens, dm.S * sizeof(int32_t), hipMemcpyDeviceToHost, hs) != hipSuccess ||
             hipMemcpyAsync(hbud, cv->budget, dm.S * sizeof(int32_t), hipMemcpyDeviceToHost, hs) !=
                 hipSuccess ||
@@ -392,8 +401,6 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
             steady += (k + dm.T - 1) / dm.T;
             tok_first += n;
             tok_steady += k;
-            max_first = std::max(max_first, n);
-            max_steady = std::max(max_steady, k);
         }
     }
     const int64_t cap_units = ((int64_t)dm.MP * dm.P + dm.T - 1) / dm.T;
@@ -469,8 +476,28 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
             const int64_t walk = (dm.G * dm.W > 8 ? 500 : 200) * (int64_t)((dm.LHkv + groups - 1) / groups);
             return own < (fused ? 3200 + std::max(share * 13 / 10, walk) : 3400 + 2 * share);
         };
-        rows_first = pays(tok_first, max_first, fused_first, rg_first) ? (int)rg : 0;
-        rows_steady = pays(tok_steady, max_steady, fused_steady, rg_steady) ? (int)rg : 0;
+        // Sessions grow by a token with every append, to their budgets and
+        // never beyond the page table, and the rule is asked again at those
+        // sizes: past rows_limit appends the later observes take the other
+        // path (one session of 450 tokens that grew to 3,150: 45 against 32
+        // us a step).  Nothing tells what a session that is empty now will be
+        // filled with, so it counts as full, to its budget.
+        const int64_t cap = (int64_t)dm.MP * dm.P;
+        auto pays_after = [&](int64_t appends, bool evicted) {
+            int64_t tokens = 0, longest = 0;
+            for (int s = 0; s < dm.S; ++s) {
+                int64_t n = hn[s] > 0 ? std::min<int64_t>(hn[s] + appends, cap) : cap;
+                if ((evicted || hn[s] <= 0) && hbud[s] >= 0) n = std::min(n, (int64_t)hbud[s] + 1);
+                tokens += n;
+                longest = std::max(longest, n);
+            }
+            return evicted ? pays(tokens, longest, fused_steady, rg_steady)
+                           : pays(tokens, longest, fused_first, rg_first);
+        };
+        rows_first = pays_after(0, false) ? (int)rg : 0;
+        rows_steady = pays_after(0, true) ? (int)rg : 0;
+        for (int64_t a = 16; rows_steady > 0 && a <= cap + 16 && rows_limit == INT64_MAX; a += 16)
+            if (!pays_after(a, true)) rows_limit = a - 16;
         dm.rows_rg = std::max(rows_first, rows_steady);
         // (the most any handle takes: handles of other sizes share the function)
         if (dm.rows_rg > 0 &&
@@ -482,7 +509,8 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         if (dm.rows_rg == 0) dm.rows_nc = rows_first = rows_steady = 0;
     }
     auto runs_multi = [&] {
-        return dm.spill || (!fused_first && rows_first == 0) || (!fused_steady && rows_steady == 0);
+        return dm.spill || (!fused_first && rows_first == 0) ||
+               (!fused_steady && (rows_steady == 0 || rows_limit != INT64_MAX));
     };
     dm.multi = runs_multi();
 
@@ -499,6 +527,11 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     if (dm.tail > 1) dm.U_cap += dm.n_wg; else dm.tail = 1;
     size_t bytes = md::scratch_bytes(dm);
     const auto too_large = [&] { return use_static && bytes > md::kStaticScratchBytes + md::row_group_words(dm.S); };
+    if (too_large() && rows_limit != INT64_MAX) {   // no room for the other path: sessions that grow stay
+        rows_limit = INT64_MAX;
+        dm.multi = runs_multi();
+        bytes = md::scratch_bytes(dm);
+    }
     if (too_large()) {
         dm.tail = 1;
         dm.U_cap = plain_units;
@@ -584,6 +617,8 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     h->rg_steady = rg_steady;
     h->rows_first = rows_first;
     h->rows_steady = rows_steady;
+    h->rows_limit = rows_limit;
+    h->appended = 0;
     h->observed = 0;
     h->word_tag = 0;
     h->phase = kNone;
@@ -621,10 +656,11 @@ md_status md_observe_step(md_handle h, int32_t step, const float* q, const uint1
         h->have_step = true;
         h->last_step = step;
         h->phase = kNone;
+        h->appended += new_k != nullptr;
         h->sel_serial = h->sel_count = nullptr;
         return MD_OK;
     }
-    const int rows = h->observed == 0 ? h->rows_first : h->rows_steady;
+    const int rows = rows_now(h, h->observed == 0);
     if (rows > 0) {
         // short sessions: the append and the observation in one launch
         hipError_t e = timed_launch_ev(h, MD_K_ATTEND, true, [&](hipEvent_t t0, hipEvent_t t1) {
@@ -632,6 +668,7 @@ md_status md_observe_step(md_handle h, int32_t step, const float* q, const uint1
         if (e == hipSuccess && h->dm.H > 0) e = md::launch_recall(h->dm, h->v, h->sc, q, abar_out, h->stream);
         if (e != hipSuccess) return MD_E_HIP;
         h->observed += 1;
+        h->appended += new_k != nullptr;
         h->have_step = true;
         h->last_step = step;
         h->phase = kObserved;
@@ -664,6 +701,7 @@ md_status md_observe_step(md_handle h, int32_t step, const float* q, const uint1
     if (e == hipSuccess && h->dm.H > 0) e = md::launch_recall(h->dm, h->v, h->sc, q, abar_out, h->stream);
     if (e != hipSuccess) return MD_E_HIP;
     h->observed += 1;
+    h->appended += new_k != nullptr;
     h->have_step = true;
     h->last_step = step;
     h->phase = kObserved;
@@ -872,8 +910,8 @@ md_status md_kernel_config(md_handle h, int32_t* out) {
     out[1] = h->dm.spill;
     out[2] = h->dm.fused ? h->dm.T : 0;
     out[3] = h->dm.n_wg;
-    out[4] = h->rows_first == 0 && h->fused_first ? 1 : 0;
-    out[5] = h->rows_steady == 0 && h->fused_steady ? 1 : 0;
+    out[4] = rows_now(h, true) == 0 && h->fused_first ? 1 : 0;
+    out[5] = rows_now(h, false) == 0 && h->fused_steady ? 1 : 0;
     out[6] = out[4] ? h->rg_first : 1;
     out[7] = out[5] ? h->rg_steady : 1;
     return MD_OK;
@@ -882,10 +920,11 @@ md_status md_kernel_config(md_handle h, int32_t* out) {
 md_status md_observe_path(md_handle h, int32_t* out) {
     if (h == nullptr || out == nullptr) return MD_E_INVALID;
     auto path = [](int rows, bool fused) { return rows > 0 ? MD_PATH_SESSION : fused ? MD_PATH_FUSED : MD_PATH_MULTI; };
-    out[0] = path(h->rows_first, h->fused_first);
-    out[1] = path(h->rows_steady, h->fused_steady);
-    out[2] = h->rows_first > 0 ? h->rows_first : h->rg_first;
-    out[3] = h->rows_steady > 0 ? h->rows_steady : h->rg_steady;
+    const int first = rows_now(h, true), steady = rows_now(h, false);
+    out[0] = path(first, h->fused_first);
+    out[1] = path(steady, h->fused_steady);
+    out[2] = first > 0 ? first : h->rg_first;
+    out[3] = steady > 0 ? steady : h->rg_steady;
     return MD_OK;
 }
 

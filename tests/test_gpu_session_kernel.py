@@ -202,3 +202,36 @@ def test_the_session_kernel_is_picked_where_it_is_the_faster_one(S, n0, window, 
         p.step()
     assert p.device_status() == 0
     p.close()
+
+
+def test_a_session_that_outgrows_the_kernel_leaves_it():
+    # one session of two rows is left to the multi-kernel path from about
+    # 1,600 tokens on: steps on either side of the change, and a step without
+    # an observation between them, match the oracle
+    w = C.with_overrides(C.get("small"), n0=1540, steps=90, obs_interval=2)
+    p = Pair(w, budgets=[4000], fused=None, max_pages=256)
+    assert p.md.observe_path()["steady"] == "session"
+    at = None
+    for k in range(90):
+        p.step()
+        if at is None and p.md.observe_path()["steady"] != "session":
+            at = k
+    assert at is not None and 10 < at < 80
+    assert p.md.observe_path()["steady"] == "multi-kernel"
+    p.md.profile(("attend", "logits"))
+    p.step()
+    p.step()
+    assert p.md.profile_read("attend")[1] == 0 and p.md.profile_read("logits")[1] == 1
+    assert p.device_status() == 0 and p.free_pages_consistent()
+    p.close()
+
+
+@pytest.mark.parametrize("max_pages,steady", [(64, "session"), (256, "multi-kernel")])
+def test_an_empty_session_counts_as_full(max_pages, steady):
+    w = C.with_overrides(C.get("small"), n0=0, steps=40)
+    p = Pair(w, n0s=[0], budgets=[4000], fused=None, max_pages=max_pages)
+    assert p.md.observe_path()["steady"] == steady
+    for _ in range(40):
+        p.step()
+    assert p.device_status() == 0
+    p.close()
