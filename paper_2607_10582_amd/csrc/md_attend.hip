@@ -16,8 +16,9 @@
 // its tokens' mass.  The key cache is read once and nothing per
 // (token, row) is written back.
 //
-// Workgroup = four waves with the same job; wave w of unit j (of nu) owns
-// the session's chunk j + w nu of 64 tokens, four tiles of 16.  Each wave
+// Workgroup = four waves with the same job; a wave of unit j (of nu) owns one
+// chunk of 64 of the session's tokens, four tiles of 16: wave w chunk 4 j + w,
+// or where pages differ in what they cost j + w nu.  Each wave
 // streams its K tiles through registers two rows ahead of the row it works
 // on, so its loads never wait for a row boundary.
 // At a row boundary the waves meet once (s_barrier, no memory fence: a fence
@@ -284,13 +285,20 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     constexpr int kTs = tstride(W, KT);
     constexpr int kTok = KT / 4;          // tokens per lane
     const int wtok0 = wv * 16 * KT;       // unit-local token of this wave's first tile
-    // The session's tokens go to its units in chunks of a wave's 64, wave w of
-    // unit j taking chunk j + w nu: the units wait for each other in every
-    // row, and neighbouring tokens are alike in what they cost (the pinned
-    // span of a quantised session stays bf16, twice the bytes).  16 sessions
-    // of 8,192 tokens, 1,024 of each pinned: 281 us a step against 315 with
-    // units of 256 neighbouring tokens; bf16 alone unchanged.
-    const int tok0 = (un.j + un.nu * wv) * 16 * KT;
+    // The units wait for each other in every row, and neighbouring tokens are
+    // alike in what they cost where pages differ: the pinned span of a
+    // quantised session stays bf16, twice the bytes, and region-aligned pages
+    // of short turns are half empty.  There (kDeal) the session's tokens go to
+    // its units in chunks of a wave's 64, wave w of unit j taking chunk
+    // j + w nu: 16 sessions of 8,192 tokens, 1,024 of each pinned, quantised,
+    // 281 us a step against 315 with units of 256 neighbouring tokens, on
+    // region-aligned pages 354 against 358.  Elsewhere a unit's waves take
+    // neighbouring chunks: as fast on pages scattered over the pool, and on
+    // consecutive ones of a power of two of rows, where chunks far apart fall
+    // on the same channels, faster (2 sessions of 64,000 tokens, 32 rows, 221
+    // us an observation against 250).
+    constexpr bool kDeal = QT || AL;
+    const int tok0 = (kDeal ? un.j + un.nu * wv : un.j * W + wv) * 16 * KT;
     bool dead = false;                    // a wait of this wave ran out: stop waiting
     // the unit's rows [r_beg, r_end)
     const int r_beg = un.r0, r_end = un.r1;
@@ -379,7 +387,7 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     {
         int slot = myslot;
         if (!myok) {   // the unit's first tile, if that has a page
-            const int p = a.page_table[(size_t)un.s * dm.MP + ((un.j * 16 * KT) >> dm.Pshift)];
+            const int p = a.page_table[(size_t)un.s * dm.MP + (((kDeal ? un.j : un.j * W) * 16 * KT) >> dm.Pshift)];
             slot = (unsigned)p < (unsigned)dm.NP ? p << dm.Pshift : 0;
         }
         kaddr = pool + (((size_t)(slot >> dm.Pshift) * dm.LHkv + r_beg) * dm.P + (slot & (dm.P - 1))) *
