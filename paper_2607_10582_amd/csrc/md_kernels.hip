@@ -89,8 +89,14 @@ struct LaneTail {
 // A full lane pass takes about 100 (lane 0, whose workgroups win the memory
 // issue) or 125 (lane 1), a pass of few units about 55.  A rest that ends no
 // later than the other lane's last pass stays whole: splitting it cost 2 %
-// (64 sessions, 172 units left after three passes each: 1,267 to 1,292 us).  pre[0 .. S) is the
-// prefix of the sessions' units, tot their sum.
+// (64 sessions, 172 units left after three passes each: 1,267 to 1,292 us).
+// So does one that fits the two claims in two groups only: over 1,468 random
+// batches of 8-72 rows (plain, 8-bit and window), three groups and more took
+// 0.68-1.03 of the time of whole sessions, 0.9 on average, two 0.94-1.11 and
+// on average 1.01 (8 rows 1.02, which four rows a group leave no more than
+// two).  (The times above are those of 56 rows; what is decided by them holds
+// for 28 to 72.)  pre[0 .. S) is the prefix of the sessions' units, tot their
+// sum.
 __device__ __forceinline__ LaneTail plan_tail(const int* pre, int S, int tot, int f, int e, int cap, int most,
                                               int tail) {
     const int lane = lane_id();
@@ -120,11 +126,11 @@ __device__ __forceinline__ LaneTail plan_tail(const int* pre, int S, int tot, in
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) um = max(um, __shfl_xor(um, o));
             int g = uni(min(tail, min(2 * cap / max(rem, 1), cap / max(um, 1))));
-            for (; g > 1; --g) {
+            for (; g > 2; --g) {
                 const int k = claim(f, e, true, g);
                 if (f + k == e || f + k + claim(f + k, e, true, g) == e) break;
             }
-            return LaneTail{f, e, max(g, 1)};
+            return LaneTail{f, e, g > 2 ? g : 1};
         }
         const bool front = t0 <= t1;
         const int k = claim(f, e, front, 1);
@@ -378,7 +384,10 @@ __global__ void __launch_bounds__(256) k_append(Dims dm, View v, Scratch sc,
         // rows alone took 130 us, as 15 groups of 4 rows about 40 us.
         // Without row groups neighbouring passes are evened out from the
         // back instead: the previous pass's last sessions move into the next
-        // one while that lowers the larger of the two passes' units.
+        // one while that lowers the larger of the two passes' units.  (With
+        // row groups a last pass of more than half the grid is left as it is:
+        // evening out nine such batches of 28 rows and more moved their times
+        // by 1.3 % at most, either way.)
         auto units = [&](int s2) { return unit_count(s_n[s2]) * rg; };
         for (int s2 = 0; s2 < dm.S; ++s2) s_pass[s2] = -1;
         int np = 0, s0 = 0;

@@ -79,7 +79,10 @@ def run(tokens, L, Hq, Hkv, P, row_groups, steps=2, window=1, aligned=False, qua
     # 17 sessions of 32 units: eight to a lane, one left, in four groups
     ("lanes", [8100] * 17, 8, 12, 2, 16, {}),
     # uneven sessions, several claims per lane, a rest of several sessions
-    ("lanes-uneven", [300 * (1 + (7 * s) % 29) for s in range(40)], 6, 8, 2, 64, {}),
+    ("lanes-uneven", [300 * (1 + (7 * s) % 29) for s in range(37)], 6, 8, 2, 64, {}),
+    # twelve of 60 units: four to a lane, and the other four would split in two
+    # groups at most, which is not done
+    ("two-groups", [15300] * 12, 8, 12, 2, 16, {}),
     # five of 100 units fit the grid, but not as two lanes of whole sessions
     ("one-pass", [25500] * 5, 4, 8, 2, 16, {}),
     # sessions of more than half a lane: three to a pass, one left
@@ -96,8 +99,8 @@ def test_last_pass_in_row_groups_agrees_with_every_row(label, tokens, L, Hq, Hkv
     n = ca["units"]
     assert n > ca["workgroups"] or label == "one-pass"
     # the groups' sums round differently, so masses that are the same to the
-    # bit come from the same plan: only the one-pass batch is split neither way
-    assert np.array_equal(a[0][0], b[0][0]) == (label == "one-pass")
+    # bit come from the same plan: two of the batches are not split
+    assert np.array_equal(a[0][0], b[0][0]) == (label in ("one-pass", "two-groups"))
     for step, (x, y) in enumerate(zip(a, b)):
         for u, v in zip(x[:3], y[:3]):
             assert np.array_equal(np.isfinite(u), np.isfinite(v))
