@@ -107,7 +107,8 @@ enum {
                                 /* skipped for the step                         */
 #define MD_DEV_TIMEOUT    0x10  /* a bounded wait between the workgroups of the */
                                 /* fused observation kernel ran out; the step's */
-                                /* attention mass is not valid                  */
+                                /* attention mass is not valid (the session     */
+                                /* kernel has no waits)                         */
 /* A void step.  A session whose decode query is not finite, or whose
  * workgroups of the fused kernel ran out of time, takes no part in the
  * step's selection (evict_count 0), compaction or quantisation, and its
@@ -405,7 +406,7 @@ md_status md_compact(md_handle h, const int32_t* evict_serial, const int32_t* ev
  * apply the library's own selection without looking at it in between.
  * Arguments, layout and requirements as for md_select_evict.  In the one
  * launch each block finds its session's places on the free list from the
- * counts of the sessions before it, with bounded waits (1 ms); a wait that
+ * counts of the sessions before it, with bounded waits (50 ms); a wait that
  * runs out, possible only while other work holds the compute units, sets
  * MD_DEV_CORRUPT: that session is left as it was (its lists are still
  * written), and the free count is then not updated, so no page can be

@@ -24,7 +24,7 @@
 // At a row boundary the waves meet once (s_barrier, no memory fence: a fence
 // would wait for the load ring) and split the row's bookkeeping:
 //   * every wave merges its own (max, sum) of the row into LDS; after the
-//     barrier, wave w merges the four partials of heads w, w + 4, ... and
+//     barrier one wave (r mod 4) merges the four partials of every head and
 //     publishes them for the other units;
 //   * for the rows it leads (every nu-th), the unit gathers every unit's
 //     statistics and publishes the row's normalisers, wave w those of heads
@@ -36,9 +36,10 @@
 // All of it but the barrier runs between the tiles of the following row.
 // Unit <-> unit hand-offs are 64-bit words (tag << 32 | float bits, the tag
 // being the step's epoch) written and polled with agent-scope atomics, so a
-// word is either absent or complete.  A unit waits only for words of rows
-// kConsumeLag or more behind its own, which every unit publishes before it
-// can wait on anything later, so the waits form no cycle.  Every wait is
+// word is either absent or complete.  In row r a unit waits only for the
+// statistics of row r - 4 (as its leader) and the normalisers of row r - 6,
+// and every unit publishes a row's statistics before it can wait for anything
+// of a later row, so the waits form no cycle.  Every wait is
 // bounded; a wait that runs out sets MD_DEV_TIMEOUT, and the wave stops
 // waiting for the rest of the step, so the grid always drains.
 
@@ -171,12 +172,6 @@ constexpr uint64_t kUnitTicks = 100000000ull;        // 1 s: a unit stops waitin
 
 __device__ __forceinline__ uint64_t now_ticks() { return __builtin_amdgcn_s_memrealtime(); }
 
-__device__ __forceinline__ void merge_stat(float& m, float& l, float m2, float l2) {
-    const float M = fmaxf(m, m2);
-    l = (M == -INFINITY) ? 0.0f : l * hw_exp2(m - M) + l2 * hw_exp2(m2 - M);
-    m = M;
-}
-
 // Wave-wide max and sum with DPP row shifts and row broadcasts (VALU only;
 // no LDS round trips).  Kogge-Stone within each 16-lane row (shifts 1, 2, 4,
 // 8; a lane whose source falls outside its row keeps the identity), then
@@ -280,7 +275,6 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
     constexpr int NT = PK ? KT / 2 : KT;   // tiles per lane after the MFMA
     const int hc = PK ? h & 7 : h;         // the lane's query head of the group
     const int ub = PK ? (h >> 3) * NT : 0; // its first tile
-    const int hh = min(hc, G - 1);         // in-bounds head for the unused columns
     constexpr int kT = 16 * W * KT;   // tokens per unit
     constexpr int kTs = tstride(W, KT);
     constexpr int kTok = KT / 4;          // tokens per lane
@@ -511,9 +505,8 @@ __device__ __forceinline__ void attend_wave(const AttendDims& dm, const AttendAr
         }
     };
 
-    // Normaliser words of row x (lane h: head h).  Every wave reads them for
-    // itself: handed on through LDS they would have to be there a row
-    // earlier, at the barrier before the row that uses them.
+    // Normaliser words of row x (lane h: head h), requested by one wave, which
+    // hands them on through LDS (check_norm).
     const bool hd_lane = lane < NH && wv + W * lane < G;
     unsigned long long nw[2];
     auto load_norm = [&](int x) {

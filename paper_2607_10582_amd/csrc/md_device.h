@@ -34,6 +34,14 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+// Softmax statistics (maximum, sum of 2^(x - maximum)) of two sets of logits
+// merged into those of both, (m, l).
+__device__ __forceinline__ void merge_stat(float& m, float& l, float m2, float l2) {
+    const float M = fmaxf(m, m2);
+    l = (M == -INFINITY) ? 0.0f : l * hw_exp2(m - M) + l2 * hw_exp2(m2 - M);
+    m = M;
+}
+
 __device__ __forceinline__ int load_agent(const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -70,12 +70,6 @@ __device__ __forceinline__ RowsLds rows_carve(unsigned char* p, int G, int nc, b
     return l;
 }
 
-__device__ __forceinline__ void fold_stat(float& m, float& l, float m2, float l2) {
-    const float M = fmaxf(m, m2);
-    l = (M == -INFINITY) ? 0.0f : l * hw_exp2(m - M) + l2 * hw_exp2(m2 - M);
-    m = M;
-}
-
 // What the append does to one session, from the counters before it and the
 // session's place among those that take a page (rank).
 struct Append {
@@ -314,8 +308,7 @@ __device__ __forceinline__ bool rows_work(const Dims& dm, const View& v, const S
         mylim = min(mylim, used);
     }
     // this wave's chunks: no wave loads tiles that hold no token, but for the
-    // last chunk's (a CU alone reads about 40 GB/s, so what a row loads sets
-    // its time)
+    // last chunk's (what a row loads sets its time)
     const int n_chunks = (n + 63) >> 6;
     const int nc = n_chunks > wv ? min(nc_cap, (n_chunks - wv + kRW - 1) / kRW) : 0;
     // window: bit 4u + i of a chunk's word marks this lane's column as blind
@@ -473,7 +466,7 @@ __device__ __forceinline__ bool rows_work(const Dims& dm, const View& v, const S
         }
         ls += __shfl_xor(ls, 16);
         ls += __shfl_xor(ls, 32);
-        fold_stat(run_m, run_l, mx, ls);
+        merge_stat(run_m, run_l, mx, ls);
         // (the maximum itself: a chunk that this column does not see weighs
         // 2^-inf = 0 in its row, not 2^(0 - M), which is infinite for M below -128)
         if (g == 0) wm[c * 16 + h] = mx;
