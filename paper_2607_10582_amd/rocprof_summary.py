@@ -4,10 +4,10 @@ Two uses:
 
 * ``trace``: per-kernel launch counts and durations from a
   ``rocprofv3 --kernel-trace --stats --output-format csv`` run, as a short
-  markdown table.  The fused kernel's launches fall into three kinds, told
-  apart by size against the median launch: md_init's residency checks
-  (under a third of it), first observations of whole prompts, the bulk
-  eviction (over twice it), and steady steps; the table gives the steady
+  markdown table.  The fused and the session kernel's launches are told apart
+  by size against the median launch: md_init's residency checks (the fused
+  kernel's; under a third of it), first observations of whole prompts, the
+  bulk eviction (over twice it), and steady steps; the table gives the steady
   and the first-observation averages apart.
 * ``hits``: L2 (TCC) hit rate of one kernel's steady launches from a
   ``--pmc TCC_HIT_sum TCC_MISS_sum`` run.
@@ -62,7 +62,7 @@ def _one(pattern: str) -> str:
 
 def kinds(values):
     """Indices of (steady, first-observation, residency-check) launches of the
-    fused kernel, by size against the median launch (steady launches are
+    fused or the session kernel, by size against the median launch (steady launches are
     most of any run)."""
     med = statistics.median(values)
     steady = [i for i, v in enumerate(values) if med / 3 <= v <= 2 * med]
@@ -82,7 +82,7 @@ def trace_table(trace_dir: str, skip: int):
     out = []
     for name, d in durs.items():
         bulk = []
-        if "k_attend" in name:
+        if "k_attend" in name or "k_rows" in name:
             st, bk, _ = kinds(d)
             steady, bulk = [d[i] for i in st], [d[i] for i in bk]
         else:
@@ -161,7 +161,7 @@ def main():
         hs_all = [v for n in names for v in hit[n]]
         ms_all = [v for n in names for v in miss[n]]
         groups = [("steady", list(range(a.skip, len(hs_all))))]
-        if a.kernel == "k_attend":
+        if a.kernel in ("k_attend", "k_rows"):
             st, bk, _ = kinds([h + m for h, m in zip(hs_all, ms_all)])
             groups = [("steady", st), ("first observation", bk)]
         print(f"| {a.kernel} launches | count | L2 (TCC) hits per launch | misses per launch | hit rate |")
