@@ -82,7 +82,7 @@ def trace_table(trace_dir: str, skip: int):
     out = []
     for name, d in durs.items():
         bulk = []
-        if "k_attend" in name or "k_rows" in name:
+        if "k_attend<" in name or "k_rows<" in name:
             st, bk, _ = kinds(d)
             steady, bulk = [d[i] for i in st], [d[i] for i in bk]
         else:
