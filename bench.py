@@ -434,7 +434,7 @@ def main():
     ap.add_argument("--no-row-groups", action="store_true",
                     help="keep every fused unit on all (layer, KV head) rows: without row groups, "
                          "batches whose units fill less than half of the fused grid take the "
-                         "multi-kernel path")
+                         "multi-kernel path or the session kernel")
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="MIB")
     ap.add_argument("--calibrate", type=int, default=0, metavar="BUCKET_STEPS",
