@@ -150,7 +150,8 @@ enum {
                                 /* and budgets at init: the session kernel (a   */
                                 /* workgroup per session and range of rows) for */
                                 /* short sessions, until appends have made them */
-                                /* too long for it (empty ones count as full);  */
+                                /* too long for it (empty ones count as full;   */
+                                /* budgets count from the first compaction on); */
                                 /* else the fused kernel, which walks the       */
                                 /* layers in order, or for small caches the     */
                                 /* multi-kernel path, parallel over layers      */
@@ -471,12 +472,14 @@ enum {
 };
 
 /* Which path the observations run on (out: 4 ints): out[0] the first
- * md_observe_step's MD_PATH_*, out[1] the later ones', out[2] and out[3] into
- * how many ranges of the L Hkv rows they split each session (the session
- * kernel, a workgroup each) or each fused unit (its row groups; a step's last
- * pass may take more); 1 on the multi-kernel path.  Sessions that outgrow
- * the session kernel as tokens are appended leave it, and out[1] and out[3]
- * then name the path from here on.  Host-only, no device work. */
+ * md_observe_step's MD_PATH_*, out[1] the later ones', once md_compact or
+ * md_select_compact has applied a selection (until then they take the session
+ * kernel only if out[0] names it, and else the fused or multi-kernel path),
+ * out[2] and out[3] into how many ranges of the L Hkv rows they split each
+ * session (the session kernel, a workgroup each) or each fused unit (its row
+ * groups; a step's last pass may take more); 1 on the multi-kernel path.
+ * Sessions that outgrow the session kernel as tokens are appended leave it,
+ * and out then names the path from here on.  Host-only, no device work. */
 md_status md_observe_path(md_handle h, int32_t* out);
 
 /*

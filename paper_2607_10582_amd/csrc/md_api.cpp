@@ -40,13 +40,16 @@ struct md_handle_s {
     int32_t last_step;
     bool fused_first;    // the first observe runs the fused kernel
     bool fused_steady;   // later observes run the fused kernel
+    bool fused_open;     // and those of them before the first compaction
     int rg_first;        // row groups of the fused units on the first observe
-    int rg_steady;       // and on later ones (1: every unit walks every row)
-    int rows_first;      // row ranges of the session kernel on the first observe
-    int rows_steady;     // and on later ones (0: the paths above)
-    int64_t rows_limit;  // appends up to which the later ones take the session kernel
+    int rg_steady;       // on later ones (1: every unit walks every row)
+    int rg_open;         // and on those of them before the first compaction
+    int rows_first;      // row ranges of the session kernel before the first compaction
+    int rows_steady;     // and after it (0: the paths above)
+    int64_t limit_first, limit_steady;   // appends up to which it is taken
     int64_t appended;    // appends enqueued (md_observe_step calls with keys)
     int64_t observed;    // observes enqueued
+    bool compacted;      // a compaction was enqueued
     Phase phase;
     const int32_t* sel_serial;   // md_select_evict's lists since the last observe
     const int32_t* sel_count;    // (NULL: no selection yet)
@@ -136,10 +139,11 @@ uint32_t next_word_tag(md_handle_s* h) {
     return h->word_tag;
 }
 
-// Row ranges of the session kernel at the next observe (0: the other paths).
-int rows_now(const md_handle_s* h, bool first) {
-    if (first) return h->rows_first;
-    return h->appended <= h->rows_limit ? h->rows_steady : 0;
+// Row ranges of the session kernel at the next observe, before the first
+// compaction or after it (0: the other paths).
+int rows_now(const md_handle_s* h, bool compacted) {
+    if (compacted) return h->appended <= h->limit_steady ? h->rows_steady : 0;
+    return h->appended <= h->limit_first ? h->rows_first : 0;
 }
 
 void release_events(md_handle_s* h) {
@@ -381,8 +385,10 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     // rg, fill a quarter of the grid.
     bool fused_first = dm.fused, fused_steady = dm.fused;
     int rg_first = 1, rg_steady = 1;
+    bool fused_open = dm.fused;   // later observes before the first compaction
+    int rg_open = 1;
     int rows_first = 0, rows_steady = 0;   // row ranges of the session kernel (0: not used)
-    int64_t rows_limit = INT64_MAX;        // appends up to which later observes use it
+    int64_t limit_first = INT64_MAX, limit_steady = INT64_MAX;   // appends up to which it is used
     const bool automatic = !(cfg->flags & (MD_FLAG_FUSED | MD_FLAG_NO_FUSED));
     int64_t first = 0, steady = 0;   // units of the first and of the later observes
     int64_t tok_first = 0, tok_steady = 0;   // and tokens
@@ -431,14 +437,17 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         auto fills = [&](int64_t u, int64_t tokens, int rg) {
             return rg > 1 ? 4 * u * rg >= dm.n_wg && tokens * rg >= share * n_cu : 2 * u >= dm.n_wg;
         };
-        fused_first = fused_steady = dm.fused;
+        rg_open = rg_steady;
+        fused_first = fused_steady = fused_open = dm.fused;
         if (!(cfg->flags & MD_FLAG_FUSED)) {
             fused_first = dm.fused && fills(first, tok_first, rg_first);
             fused_steady = dm.fused && fills(steady, tok_steady, rg_steady);
+            fused_open = dm.fused && fills(steady, tok_first, rg_open);   // not held to the budgets yet
         }
         if (!fused_first) rg_first = 1;
         if (!fused_steady) rg_steady = 1;
-        dm.rg_max = std::max(rg_first, rg_steady);
+        if (!fused_open) rg_open = 1;
+        dm.rg_max = std::max({rg_first, rg_steady, rg_open});
         dm.U_cap = dm.fused ? base_units * dm.rg_max : base_units;
     };
     choose_paths(rows_ok);
@@ -478,10 +487,13 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         };
         // Sessions grow by a token with every append, to their budgets and
         // never beyond the page table, and the rule is asked again at those
-        // sizes: past rows_limit appends the later observes take the other
-        // path (one session of 450 tokens that grew to 3,150: 45 against 32
-        // us a step).  Nothing tells what a session that is empty now will be
-        // filled with, so it counts as full, to its budget.
+        // sizes: past the limit's appends the observes take the other path
+        // (one session of 450 tokens that grew to 3,150: 45 against 32 us a
+        // step).  Nothing tells what a session that is empty now will be
+        // filled with, so it counts as full, to its budget.  And until a
+        // compaction no session is held to its budget: a program may observe
+        // and select without applying it (ten prompts of 400-2,600 tokens,
+        // budgets of a quarter: 88 us a pass on this kernel against 75).
         const int64_t cap = (int64_t)dm.MP * dm.P;
         auto pays_after = [&](int64_t appends, bool evicted) {
             int64_t tokens = 0, longest = 0;
@@ -496,8 +508,13 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         };
         rows_first = pays_after(0, false) ? (int)rg : 0;
         rows_steady = pays_after(0, true) ? (int)rg : 0;
-        for (int64_t a = 16; rows_steady > 0 && a <= cap + 16 && rows_limit == INT64_MAX; a += 16)
-            if (!pays_after(a, true)) rows_limit = a - 16;
+        auto limit = [&](bool evicted) -> int64_t {
+            for (int64_t a = 16; a <= cap + 16; a += 16)
+                if (!pays_after(a, evicted)) return a - 16;
+            return INT64_MAX;
+        };
+        if (rows_first > 0) limit_first = limit(false);
+        if (rows_steady > 0) limit_steady = limit(true);
         dm.rows_rg = std::max(rows_first, rows_steady);
         // (the most any handle takes: handles of other sizes share the function)
         if (dm.rows_rg > 0 &&
@@ -509,8 +526,8 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
         if (dm.rows_rg == 0) dm.rows_nc = rows_first = rows_steady = 0;
     }
     auto runs_multi = [&] {
-        return dm.spill || (!fused_first && rows_first == 0) ||
-               (!fused_steady && (rows_steady == 0 || rows_limit != INT64_MAX));
+        return dm.spill || (!(fused_first && fused_open) && (rows_first == 0 || limit_first != INT64_MAX)) ||
+               (!fused_steady && (rows_steady == 0 || limit_steady != INT64_MAX));
     };
     dm.multi = runs_multi();
 
@@ -527,8 +544,9 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     if (dm.tail > 1) dm.U_cap += dm.n_wg; else dm.tail = 1;
     size_t bytes = md::scratch_bytes(dm);
     const auto too_large = [&] { return use_static && bytes > md::kStaticScratchBytes + md::row_group_words(dm.S); };
-    if (too_large() && rows_limit != INT64_MAX) {   // no room for the other path: sessions that grow stay
-        rows_limit = INT64_MAX;
+    if (too_large() && dm.rows_rg > 0) {   // no room for another path: no observe changes to it later
+        limit_first = limit_steady = INT64_MAX;
+        if (fused_first && rows_first == 0) rows_first = rows_steady;
         dm.multi = runs_multi();
         bytes = md::scratch_bytes(dm);
     }
@@ -613,13 +631,17 @@ static md_status init_handle(const md_config* cfg, const md_region_params* rp, c
     h->last_step = 0;
     h->fused_first = fused_first;
     h->fused_steady = fused_steady;
+    h->fused_open = fused_open;
     h->rg_first = rg_first;
     h->rg_steady = rg_steady;
+    h->rg_open = rg_open;
     h->rows_first = rows_first;
     h->rows_steady = rows_steady;
-    h->rows_limit = rows_limit;
+    h->limit_first = limit_first;
+    h->limit_steady = limit_steady;
     h->appended = 0;
     h->observed = 0;
+    h->compacted = false;
     h->word_tag = 0;
     h->phase = kNone;
     h->sel_serial = nullptr;
@@ -660,7 +682,7 @@ md_status md_observe_step(md_handle h, int32_t step, const float* q, const uint1
         h->sel_serial = h->sel_count = nullptr;
         return MD_OK;
     }
-    const int rows = rows_now(h, h->observed == 0);
+    const int rows = rows_now(h, h->compacted);
     if (rows > 0) {
         // short sessions: the append and the observation in one launch
         hipError_t e = timed_launch_ev(h, MD_K_ATTEND, true, [&](hipEvent_t t0, hipEvent_t t1) {
@@ -675,8 +697,8 @@ md_status md_observe_step(md_handle h, int32_t step, const float* q, const uint1
         h->sel_serial = h->sel_count = nullptr;
         return MD_OK;
     }
-    const bool fused = h->observed == 0 ? h->fused_first : h->fused_steady;
-    const int rg = fused ? (h->observed == 0 ? h->rg_first : h->rg_steady) : 1;
+    const bool fused = h->observed == 0 ? h->fused_first : h->compacted ? h->fused_steady : h->fused_open;
+    const int rg = h->observed == 0 ? h->rg_first : h->compacted ? h->rg_steady : h->rg_open;
     hipError_t e = timed_launch(h, MD_K_APPEND, [&] {
         return md::launch_append(h->dm, h->v, h->sc, new_k, new_region, fused ? 1 : 0, 1, rg, next_word_tag(h),
                                  h->stream); });
@@ -767,6 +789,7 @@ md_status md_compact(md_handle h, const int32_t* evict_serial, const int32_t* ev
         hipSuccess)
         return MD_E_HIP;
     h->phase = kCompacted;
+    h->compacted = true;
     h->sel_serial = h->sel_count = nullptr;
     return MD_OK;
 }
@@ -787,6 +810,7 @@ md_status md_select_compact(md_handle h, int32_t* evict_serial, int32_t* evict_c
                                     h->stream); }) != hipSuccess)
         return MD_E_HIP;
     h->phase = kCompacted;
+    h->compacted = true;
     h->sel_serial = h->sel_count = nullptr;
     return MD_OK;
 }
@@ -910,8 +934,8 @@ md_status md_kernel_config(md_handle h, int32_t* out) {
     out[1] = h->dm.spill;
     out[2] = h->dm.fused ? h->dm.T : 0;
     out[3] = h->dm.n_wg;
-    out[4] = rows_now(h, true) == 0 && h->fused_first ? 1 : 0;
-    out[5] = rows_now(h, false) == 0 && h->fused_steady ? 1 : 0;
+    out[4] = rows_now(h, false) == 0 && h->fused_first ? 1 : 0;
+    out[5] = rows_now(h, true) == 0 && h->fused_steady ? 1 : 0;
     out[6] = out[4] ? h->rg_first : 1;
     out[7] = out[5] ? h->rg_steady : 1;
     return MD_OK;
@@ -920,7 +944,7 @@ md_status md_kernel_config(md_handle h, int32_t* out) {
 md_status md_observe_path(md_handle h, int32_t* out) {
     if (h == nullptr || out == nullptr) return MD_E_INVALID;
     auto path = [](int rows, bool fused) { return rows > 0 ? MD_PATH_SESSION : fused ? MD_PATH_FUSED : MD_PATH_MULTI; };
-    const int first = rows_now(h, true), steady = rows_now(h, false);
+    const int first = rows_now(h, false), steady = rows_now(h, true);
     out[0] = path(first, h->fused_first);
     out[1] = path(steady, h->fused_steady);
     out[2] = first > 0 ? first : h->rg_first;

@@ -235,3 +235,24 @@ def test_an_empty_session_counts_as_full(max_pages, steady):
         p.step()
     assert p.device_status() == 0
     p.close()
+
+
+def test_prompts_that_are_never_compacted_keep_their_path():
+    # one prompt of 2,600 tokens (56 rows) is too long for the session kernel,
+    # what its budget leaves of it is not: observed and selected again and
+    # again it stays on the other path, until a selection is applied
+    w = C.with_overrides(C.get("small"), L=28, S=1, n0=None, n0_range=(1, 2), steps=6)
+    p = Pair(w, n0s=[2600], budgets=[600], oracle_sessions=[], fused=None)
+    path = p.md.observe_path()
+    assert path["first"] != "session" and path["steady"] == "session"
+    p.md.profile(("append",))
+    for k in range(1, 6):
+        q, nk, reg, *_ = p.inputs(k)
+        p.md.observe(k, q, nk, reg)
+        p.md.score()
+        p.md.select()
+        assert p.md.profile_read("append")[1] == (1 if k < 5 else 0), k
+        if k == 4:
+            p.md.compact()
+    assert p.md.device_status() == 0
+    p.close()
